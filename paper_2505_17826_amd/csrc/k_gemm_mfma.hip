@@ -1037,7 +1037,7 @@ static int store_tile_env() {
 
 // Compute units of the current device (cached per device; host threads may
 // call concurrently, so the cache entries are atomic).
-static hipError_t cu_count(int* n) {
+hipError_t cu_count(int* n) {
   static std::atomic<int> cache[64];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);

@@ -151,7 +151,7 @@ FwdWs carve_fwd(void* base, const rft_tokens& tok, int64_t d, int64_t V, int dty
   const int64_t hrows = blocked ? round_up(tok.T > 0 ? tok.T : 1, 256) : (tok.T > 0 ? tok.T : 1);
   w.hc = dtype == RFT_BF16 ? c.take<uint16_t>((size_t)hrows * d) : nullptr;
   w.wb = blocked ? c.take<uint16_t>((size_t)round_up(V, 256) * d) : nullptr;
-  int tn = dtype == RFT_BF16 ? kMfmaTileN : kSimtTileN;
+  int tn = dtype == RFT_BF16 ? kMfmaTileN : kF32TileN;
   w.ntiles = (int)((V + tn - 1) / tn);
   w.ldp = tok.T > 0 ? tok.T : 1;
   w.pm = c.take<float>((size_t)w.ntiles * w.ldp);
@@ -561,7 +561,7 @@ rft_status rft_token_logprobs(const rft_tokens* tok, const void* hidden, const v
                            tok->token_ids, w.m.meta, 0, tok->T, w.pm, w.ps, w.pu, w.ldp, w.zy, s),
             fn);
   } else {
-    RFT_HIP(simt_fwd_stats((const float*)hidden, d, (const float*)weight, V, w.m.rows,
+    RFT_HIP(f32_fwd_stats((const float*)hidden, d, (const float*)weight, V, w.m.rows,
                            tok->token_ids, w.m.meta, tok->T, w.pm, w.ps, w.pu, w.ldp, w.zy, s),
             fn);
   }
@@ -671,16 +671,16 @@ rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, cons
     const float* W = (const float*)weight;
     for (int64_t ci = 0; ci < nchunks; ++ci) {
       int64_t c0 = ci * Tc;
-      RFT_HIP(simt_dz(H, d, W, V, w.Vpad, w.m.rows, tok->token_ids, lse, grad_logp,
-                      grad_entropy, entropy, cnt, c0, Tc, w.dz32, s),
+      RFT_HIP(f32_dz(H, d, W, V, w.Vpad, w.m.rows, tok->token_ids, lse, grad_logp, grad_entropy,
+                     entropy, cnt, c0, Tc, w.dz32, s),
               fn);
-      // dH[m, j] = sum_v dZ[m, v] W[v, j]
-      RFT_HIP(simt_gemm_store(w.dz32, w.Vpad, 1, W, 1, d, nullptr, 0, Tc, d, V, cnt, c0, Tc, 1, 0,
-                              d_hidden, d, w.m.rows, c0, 0, s),
+      // d_weight is overwritten by this chunk's dW: until then it is free for
+      // the partial sums of a dH whose few rows need K split
+      const bool fresh = ci == 0 && !accumulate_dw;
+      RFT_HIP(f32_dh(w.dz32, w.Vpad, W, V, d, Tc, cnt, c0, w.m.rows, d_hidden,
+                     fresh ? d_weight : nullptr, fresh ? V * d : 0, s),
               fn);
-      // dW[v, j] = sum_t dZ[t, v] H[rows[c0 + t], j]
-      RFT_HIP(simt_gemm_store(w.dz32, 1, w.Vpad, H, 1, d, w.m.rows, c0, V, d, Tc, cnt, c0, Tc, 0, 1,
-                              d_weight, d, nullptr, 0, (ci > 0 || accumulate_dw) ? 1 : 0, s),
+      RFT_HIP(f32_dw(w.dz32, w.Vpad, H, d, V, Tc, cnt, c0, w.m.rows, d_weight, fresh ? 0 : 1, s),
               fn);
     }
     if (nchunks == 0 && !accumulate_dw) RFT_HIP(launch_fill_zero(d_weight, V * d, s), fn);

@@ -323,18 +323,21 @@ hipError_t mfma_gemm_store(const uint16_t* A, int64_t lda, const uint16_t* B, in
                            int64_t cnt_cap, int m_from_cnt, int k_from_cnt, float* C, int64_t ldc,
                            const int32_t* rows, int64_t rows_off, int accumulate, hipStream_t s,
                            int a_blk = 0, int b_blk = 0);
-hipError_t simt_fwd_stats(const float* H, int64_t d, const float* W, int64_t V, const int32_t* rows,
-                          const int32_t* ids, const int32_t* cnt, int64_t cap, float* pm, float* ps,
-                          float* pu, int64_t ldp, float* zy, hipStream_t s);
-hipError_t simt_dz(const float* H, int64_t d, const float* W, int64_t V, int64_t Vpad,
-                   const int32_t* rows, const int32_t* ids, const float* lse, const float* cgrad,
-                   const float* egrad, const float* ent, const int32_t* cnt, int64_t c0,
-                   int64_t Tc, float* dz, hipStream_t s);
-hipError_t simt_gemm_store(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn,
-                           int64_t sbk, const int32_t* b_map, int64_t b_koff, int64_t M, int64_t N,
-                           int64_t K, const int32_t* cnt, int64_t cnt_off, int64_t cnt_cap,
-                           int m_from_cnt, int k_from_cnt, float* C, int64_t ldc,
-                           const int32_t* rows, int64_t rows_off, int accumulate, hipStream_t s);
+// Compute units of the current device (cached per device).
+hipError_t cu_count(int* n);
+hipError_t f32_fwd_stats(const float* H, int64_t d, const float* W, int64_t V, const int32_t* rows,
+                         const int32_t* ids, const int32_t* cnt, int64_t cap, float* pm, float* ps,
+                         float* pu, int64_t ldp, float* zy, hipStream_t s);
+hipError_t f32_dz(const float* H, int64_t d, const float* W, int64_t V, int64_t Vpad,
+                  const int32_t* rows, const int32_t* ids, const float* lse, const float* cgrad,
+                  const float* egrad, const float* ent, const int32_t* cnt, int64_t c0,
+                  int64_t Tc, float* dz, hipStream_t s);
+hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int64_t d, int64_t Tc,
+                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* scratch,
+                  int64_t scratch_elems, hipStream_t s);
+hipError_t f32_dw(const float* dz, int64_t Vpad, const float* H, int64_t d, int64_t V, int64_t Tc,
+                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dW, int accumulate,
+                  hipStream_t s);
 hipError_t launch_gather_rows16(const uint16_t* H, int64_t d, const int32_t* rows,
                                 const int32_t* cnt, int64_t cap, uint16_t* Hc, hipStream_t s);
 hipError_t launch_fill_zero(float* out, int64_t n, hipStream_t s);
@@ -360,6 +363,6 @@ constexpr int kMfmaTileN = 256;  // vocabulary columns per forward tile (bf16 pa
 __host__ __device__ constexpr int64_t blk_index(int64_t r, int64_t k, int64_t Kp) {
   return (((r >> 8) * (Kp >> 6) + (k >> 6)) << 14) + ((r & 255) << 6) + (k & 63);
 }
-constexpr int kSimtTileN = 64;   // (fp32 path)
+constexpr int kF32TileN = 64;    // (fp32 path)
 
 }  // namespace rft
