@@ -36,6 +36,7 @@
 //              optionally added to the existing values.  On tile-blocked
 //              operands (dH, dW of the step) k_gemm384 does this on a
 //              384 x 256 tile (fewer operand bytes per flop).
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 
@@ -102,7 +103,10 @@ struct Args {
   uint16_t* dzt; int64_t ldzt;                                //   and dZ^T [Vpad, ldzt] blocked (nullptr = none)
   float* C; int64_t ldc; int accumulate; int c_scatter;  // EPI_STORE
   int sel;            // EPI_STORE with both tile sizes launched: 1 = the 384-row kernel runs
-  int ncu;            //   only if prefer384(M, N, ncu), 2 = the 256-row kernel only if not
+  int ncu;            //   only if prefer384(M, N, slices, ncu), 2 = the 256-row kernel only if not
+  // EPI_STORE over slices of K (pick_slices): slice s of an M x N result goes
+  // to part + s M N (row m at m N), summed by k_sum_slices; 0 = never
+  float* part; int64_t part_elems;
 };
 
 // fp32-store GEMM on tile-blocked operands: whether the 384 x 256 tile beats
@@ -112,11 +116,57 @@ struct Args {
 // work at ~5% more flops per cycle, measured on the 7B shapes).  E.g. d_hidden
 // of 131072 rows and d = 3584: 19 rounds of 384 (27.2) against 28 of 256;
 // with d = 1536: 9 (12.9) against 12; 36901 rows, d = 3584: 6 (8.6) against 8.
-__host__ __device__ inline bool prefer384(int64_t M, int64_t N, int64_t ncu) {
-  const int64_t tn = (N + 255) / 256;
+// Slices of K multiply the tiles of both.
+__host__ __device__ inline bool prefer384(int64_t M, int64_t N, int64_t slices, int64_t ncu) {
+  const int64_t tn = (N + 255) / 256 * slices;
   const int64_t r4 = ((M + 383) / 384 * tn + ncu - 1) / ncu;
   const int64_t r2 = ((M + 255) / 256 * tn + ncu - 1) / ncu;
   return r4 * 143 < r2 * 100;
+}
+
+// Slices of K for an M x N result with K long and few tiles (d_hidden of a
+// micro-batch: 5 x 14 tiles of 256 x 256 at 1152 rows, d = 3584, each K =
+// 152064 long, ran on 70 of 256 CUs: 3.5 ms whatever the rows).  Lane l of the
+// wave prices l + 1 slices and the cheapest wins: rounds of tiles over the
+// CUs, each a slice of K long (26 ns per K for a 256 x 256 tile per CU, 3 us
+// for its start and its stores), plus the pass over the partial sums (8 bytes
+// per element and slice at 5 TB/s, 5 us for its launch).  At most kMaxSlices
+// slices, kSliceRounds rounds (the grid's size) and the scratch; one slice from
+// kSliceRounds / 2 rounds on, where the last round weighs little.  Every wave
+// of the GEMM and of the sum computes the same number from the same count.
+// Independent of the tile, so both tiles give the same bits.  Measured at d =
+// 3584, V = 152064: 1152 rows 3.52 -> 1.19 ms, 2560 rows 3.57 -> 2.30 ms, and
+// 26 / 69 us for the sum.
+constexpr int kMaxSlices = 16, kSliceRounds = 6;
+__device__ __forceinline__ int pick_slices(int M, int N, int K, int ncu, int64_t part_elems) {
+  const int64_t t64 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  if (t64 == 0 || 2 * t64 >= (int64_t)kSliceRounds * ncu) return 1;
+  // integers (M N < 2^26 here): the same in every kernel whatever the compiler
+  // contracts
+  const int tiles = (int)t64, S = 1 + (int)(threadIdx.x & 63);
+  int cost = (tiles * S + ncu - 1) / ncu * (26 * K / S + 3000);
+  if (S > 1) cost += 5000 + M * N / 625 * S;
+  const bool ok = S == 1 || (S <= kMaxSlices && tiles * S <= kSliceRounds * ncu &&
+                             (int64_t)S * M * N <= part_elems && S * BK <= K);
+  if (!ok) cost = 0x7fffffff;
+  int best = cost;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, 64));
+  return 1 + (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(cost == best));
+}
+
+// Item b of an S-sliced M x N result: XCD b % 8 takes a contiguous run of
+// (slice, tile) items, tiles of one slice together, so the tiles that run on
+// one XCD read the same K range of both operands through its L2.
+__device__ __forceinline__ bool slice_of(int b, int nTm, int nTn, int S, int& sl, int& mt, int& nt) {
+  const int items = nTm * nTn * S, per = (items + 7) / 8;
+  const int i = (b & 7) * per + (b >> 3);
+  if ((b >> 3) >= per || i >= items) return false;
+  sl = i / (nTm * nTn);
+  const int t = i - sl * (nTm * nTn);
+  mt = t % nTm;
+  nt = t / nTm;
+  return true;
 }
 
 // Raw buffer descriptor (wave-uniform) over `bytes` bytes from p.
@@ -294,13 +344,20 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
   const int N = g.N;
   const int NB = g.NB > 0 ? g.NB : N;
   if (EPI == EPI_STORE && g.k_from_cnt && K == 0 && g.accumulate) return;  // nothing to add
-  if (EPI == EPI_STORE && g.sel == 2 && prefer384(M, N, g.ncu)) return;  // the 384-row kernel's
+  int S = 1, sl = 0;
+  if (EPI == EPI_STORE && g.part) S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, K, g.ncu, g.part_elems));
+  if (EPI == EPI_STORE && g.sel == 2 && prefer384(M, N, S, g.ncu)) return;  // the 384-row kernel's
   const int nTm = (M + BM - 1) / BM, nTn = (N + BN - 1) / BN;
   // The grid is sized for the largest possible M; workgroups without a tile
   // for the device count exit at once.
   int mt, nt;
-  if (!tile_of<kSG<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) return;
-  const int nk = (K + BK - 1) / BK;
+  if (EPI == EPI_STORE && S > 1) {
+    if (!slice_of((int)blockIdx.x, nTm, nTn, S, sl, mt, nt)) return;
+  } else if (!tile_of<kSG<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) {
+    return;
+  }
+  const int nkt = (K + BK - 1) / BK, ks0 = EPI == EPI_STORE ? sl * ((nkt + S - 1) / S) : 0;
+  const int nk = EPI == EPI_STORE && S > 1 ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
 
   // per-lane load geometry (see load_stage): row w*64 + p*8 + (lane>>3)
   constexpr int NLOAD = kNLoad<EPI>;
@@ -383,11 +440,11 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
       for (int j = 0; j < 8; ++j) acc4[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
 
     char* const ldsw = lds + (wid % NLOAD) * ((256 / NLOAD) * 128);
-    if (nk > 0 && loader) load_stage<NLOAD>(rA, rB, ldsw, 0, K, lg);
+    if (nk > 0 && loader) load_stage<NLOAD>(rA, rB, ldsw, ks0 * BK, K, lg);
     __syncthreads();  // first stage and the per-row parameters are visible to every wave
     for (int kt = 0; kt < nk; ++kt) {
       if (kt + 1 < nk && loader)
-        load_stage<NLOAD>(rA, rB, ldsw + ((kt + 1) & 1) * STAGE, (kt + 1) * BK, K, lg);
+        load_stage<NLOAD>(rA, rB, ldsw + ((kt + 1) & 1) * STAGE, (ks0 + kt + 1) * BK, K, lg);
       const char* As = lds + (kt & 1) * STAGE;
       const char* Bs = As + A_BYTES;
       {
@@ -646,14 +703,15 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
           const int rl = wm * 64 + i * 16 + q4 * 4 + q;
           const int m = m0 + rl;
           if (m >= M) continue;
-          const int64_t dst = (int64_t)rp_i[rl] * g.ldc;
+          float* const dst = S > 1 ? g.part + ((int64_t)sl * M + m) * N : g.C + (int64_t)rp_i[rl] * g.ldc;
+          const bool add = g.accumulate && S == 1;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int col = n0 + wn * 128 + j * 16 + r16;
             if (col < N) {
               float v = acc4[i][j][q];
-              if (g.accumulate) v += g.C[dst + col];
-              g.C[dst + col] = v;
+              if (add) v += dst[col];
+              dst[col] = v;
             }
           }
         }
@@ -709,11 +767,18 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   }
   const int N = g.N;
   if (EPI == EPI_STORE && g.k_from_cnt && K == 0 && g.accumulate) return;  // nothing to add
-  if (EPI == EPI_STORE && g.sel == 1 && !prefer384(M, N, g.ncu)) return;  // the 256-row kernel's
+  int S = 1, sl = 0;
+  if (EPI == EPI_STORE && g.part) S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, K, g.ncu, g.part_elems));
+  if (EPI == EPI_STORE && g.sel == 1 && !prefer384(M, N, S, g.ncu)) return;  // the 256-row kernel's
   const int nTm = (M + BM4 - 1) / BM4, nTn = (N + BN - 1) / BN;
   int mt, nt;
-  if (!tile_of<kSG4<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) return;
-  const int nk = (K + BK - 1) / BK;
+  if (EPI == EPI_STORE && S > 1) {
+    if (!slice_of((int)blockIdx.x, nTm, nTn, S, sl, mt, nt)) return;
+  } else if (!tile_of<kSG4<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) {
+    return;
+  }
+  const int nkt = (K + BK - 1) / BK, ks0 = EPI == EPI_STORE ? sl * ((nkt + S - 1) / S) : 0;
+  const int nk = EPI == EPI_STORE && S > 1 ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
   constexpr int NLOAD = kNLoad4<EPI>;
   constexpr int RA = BM4 / NLOAD, RB = BN / NLOAD;  // rows of A and of B per loader wave
   static_assert(RA % 16 == 0 && RB % 16 == 0, "offset parity follows the row-pair swizzle");
@@ -761,10 +826,10 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   for (int i = 0; i < 6; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc4[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  if (nk > 0 && loader) load(lds, 0);
+  if (nk > 0 && loader) load(lds, ks0 * BK);
   __syncthreads();  // first stage visible to every wave
   for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk && loader) load(lds + ((kt + 1) & 1) * STAGE4, (kt + 1) * BK);
+    if (kt + 1 < nk && loader) load(lds + ((kt + 1) & 1) * STAGE4, (ks0 + kt + 1) * BK);
     const char* As = lds + (kt & 1) * STAGE4;
     const char* Al = As + (wm * 96 + r16) * 128;
     const char* Bl = As + A_BYTES4 + (wn * 128 + r16) * 128;
@@ -803,14 +868,16 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
       for (int q = 0; q < 4; ++q) {
         const int m = m0 + wm * 96 + i * 16 + q4 * 4 + q;
         if (m >= M) continue;
-        const int64_t dst = (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
+        float* const dst = S > 1 ? g.part + ((int64_t)sl * M + m) * N
+                                 : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
+        const bool add = g.accumulate && S == 1;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const int col = n0 + wn * 128 + j * 16 + r16;
           if (col < N) {
             float v = acc4[i][j][q];
-            if (g.accumulate) v += g.C[dst + col];
-            g.C[dst + col] = v;
+            if (add) v += dst[col];
+            dst[col] = v;
           }
         }
       }
@@ -1013,6 +1080,27 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   }
 }
 
+typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // rows of the caller's buffer
+// C[rows[rows_off + m], n] = the sum over the slices of part, in slice order
+// (nothing to do when the GEMM took one slice).
+__global__ void __launch_bounds__(256) k_sum_slices(const Args g) {
+  int64_t c = (int64_t)g.cnt[0] - g.cnt_off;
+  const int M = (int)(c < 0 ? 0 : (c > g.cnt_cap ? g.cnt_cap : c)), N = g.N;
+  const int S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, g.K, g.ncu, g.part_elems));
+  if (S == 1) return;
+  const int64_t MN = (int64_t)M * N;
+  for (int m = blockIdx.x; m < M; m += gridDim.x) {
+    float* const dst = g.C + (int64_t)g.rows[g.rows_off + m] * g.ldc;
+    const float* const src = g.part + (int64_t)m * N;
+    for (int n = threadIdx.x * 4; n < N; n += 1024) {  // N is a multiple of 8
+      floatx4 v = *(const floatx4*)(src + n);
+#pragma unroll 4
+      for (int s = 1; s < S; ++s) v += *(const floatx4*)(src + s * MN + n);
+      *(floatx4_a4*)(dst + n) = v;
+    }
+  }
+}
+
 }  // namespace mf
 
 // ------------------------------------------------------------ launchers ----
@@ -1149,54 +1237,62 @@ hipError_t mfma_dz(const uint16_t* Hc, int64_t d, const uint16_t* W, int64_t V, 
   return hipGetLastError();
 }
 
-// C[M, N] (+)= A[M, K] . B[N, K]^T with fp32 output; optional row scatter of C
-// through rows[rows_off + m]; M or K can come from the device counter.  A
-// blocked operand (a_blk / b_blk) has ld = Kp and whole 256-row panels whose
-// rows past M (N) and columns past K hold zeros.
+// C[M, N] (+)= A[M, K] . B[N, K]^T with fp32 output, both operands tile-blocked
+// (ld = Kp, whole 256-row panels whose rows past M (N) and columns past K hold
+// zeros); optional row scatter of C through rows[rows_off + m]; M or K can come
+// from the device counter.  With M from the counter and `part` (part_elems fp32
+// values of scratch), K may be split into slices (pick_slices; N a multiple of
+// 4, no accumulation).
 hipError_t mfma_gemm_store(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb,
                            int64_t M, int64_t N, int64_t K, const int32_t* cnt, int64_t cnt_off,
                            int64_t cnt_cap, int m_from_cnt, int k_from_cnt, float* C, int64_t ldc,
                            const int32_t* rows, int64_t rows_off, int accumulate, hipStream_t s,
-                           int a_blk, int b_blk) {
+                           float* part, int64_t part_elems) {
   mf::Args a = {};
   a.A = A; a.lda = lda; a.B = B; a.ldb = ldb;
-  a.a_blk = a_blk; a.b_blk = b_blk;
+  a.a_blk = 1; a.b_blk = 1;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.cnt = cnt; a.cnt_off = cnt_off; a.cnt_cap = cnt_cap; a.m_from_cnt = m_from_cnt;
   a.k_from_cnt = k_from_cnt;
   a.C = C; a.ldc = ldc; a.rows = rows; a.rows_off = rows_off; a.c_scatter = rows != nullptr;
   a.accumulate = accumulate;
-  // tile-blocked operands: the 384 x 256 tile where its one descriptor over
-  // two panels of A and its scalar offsets fit 32 bits, K needs no tail and
-  // it takes fewer rounds of tiles (prefer384).  With the rows on the device
-  // both kernels are launched with the same test there: the other one's
-  // workgroups return at once (a few microseconds).  RFT_GEMM_STORE_TILE=256
-  // or 384 in the environment fixes the choice (the results are the same bit
-  // for bit).
+  // the 384 x 256 tile where its one descriptor over two panels of A and its
+  // scalar offsets fit 32 bits, K needs no tail and it takes fewer rounds of
+  // tiles (prefer384).  With the rows on the device both kernels are launched
+  // with the same test there: the other one's workgroups return at once (a
+  // few microseconds).  RFT_GEMM_STORE_TILE=256 or 384 in the environment
+  // fixes the choice (the results are the same bit for bit).
   const int force = store_tile_env();
-  if (a_blk && b_blk && fits384(lda, ldb, K, k_from_cnt) && force != 256) {
-    int ncu = 0;
-    hipError_t e = cu_count(&ncu);
-    if (e != hipSuccess) return e;
-    if (force == 384) {
-      mf::k_gemm384<mf::EPI_STORE><<<grid_for384<mf::EPI_STORE>(M, N), mf::NT, 0, s>>>(a);
-      return hipGetLastError();
-    }
-    if (!m_from_cnt) {
-      if (mf::prefer384(M, N, ncu)) {
-        mf::k_gemm384<mf::EPI_STORE><<<grid_for384<mf::EPI_STORE>(M, N), mf::NT, 0, s>>>(a);
-        return hipGetLastError();
-      }
-    } else {
-      a.ncu = ncu;
-      a.sel = 1;
-      mf::k_gemm384<mf::EPI_STORE><<<grid_for384<mf::EPI_STORE>(M, N), mf::NT, 0, s>>>(a);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      a.sel = 2;
-    }
+  int ncu = 0;
+  hipError_t e = cu_count(&ncu);
+  if (e != hipSuccess) return e;
+  a.ncu = ncu;
+  const bool sliced = part && m_from_cnt && !k_from_cnt && !accumulate && rows && M > 0 && N % 4 == 0;
+  if (sliced) {
+    a.part = part;
+    a.part_elems = part_elems;
   }
-  mf::k_gemm<mf::EPI_STORE><<<grid_for<mf::EPI_STORE>(M, N), mf::NT, 0, s>>>(a);
-  return hipGetLastError();
+  // a sliced result has at most kSliceRounds rounds of items
+  const unsigned least = sliced ? (unsigned)(mf::kSliceRounds * ncu + 8) : 0u;
+  const unsigned g4 = std::max(grid_for384<mf::EPI_STORE>(M, N), least);
+  const unsigned g2 = std::max(grid_for<mf::EPI_STORE>(M, N), least);
+  const bool can384 = fits384(lda, ldb, K, k_from_cnt) && force != 256;
+  const bool only384 = can384 && (force == 384 || (!m_from_cnt && mf::prefer384(M, N, 1, ncu)));
+  if (only384 || (can384 && m_from_cnt)) {
+    a.sel = only384 ? 0 : 1;
+    mf::k_gemm384<mf::EPI_STORE><<<g4, mf::NT, 0, s>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    a.sel = 2;
+  }
+  if (!only384) {
+    mf::k_gemm<mf::EPI_STORE><<<g2, mf::NT, 0, s>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (sliced) {
+    mf::k_sum_slices<<<(unsigned)std::min<int64_t>(M, 4096), 256, 0, s>>>(a);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace rft

@@ -656,13 +656,15 @@ rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, cons
                       grad_entropy, entropy, cnt, c0, Tc, w.dz, w.dzt, Tc, s),
               fn);
       RFT_HIP(launch_transpose_blk(w.hc, d, cnt, c0, Tc, Tc, w.dpad, w.hct, s), fn);
-      // dH rows of this chunk: dZ [count, Vpad] . Wt[d, Vpad]^T, scattered to token rows
-      RFT_HIP(mfma_gemm_store(w.dz, w.Vpad, w.wt, w.Vpad, Tc, d, w.Vpad, cnt, c0, Tc, 1, 0,
-                              d_hidden, d, w.m.rows, c0, 0, s, 1, 1),
-              fn);
       // dW += dZ^T . Hc over the chunk's rows, both operands K-contiguous (K = rows)
       RFT_HIP(mfma_gemm_store(w.dzt, Tc, w.hct, Tc, V, d, Tc, cnt, c0, Tc, 0, 1, d_weight, d,
-                              nullptr, 0, (ci > 0 || accumulate_dw) ? 1 : 0, s, 1, 1),
+                              nullptr, 0, (ci > 0 || accumulate_dw) ? 1 : 0, s),
+              fn);
+      // dH rows of this chunk: dZ [count, Vpad] . Wt[d, Vpad]^T, scattered to
+      // token rows; dZ^T is no longer needed and holds the partial sums where
+      // K is split
+      RFT_HIP(mfma_gemm_store(w.dz, w.Vpad, w.wt, w.Vpad, Tc, d, w.Vpad, cnt, c0, Tc, 1, 0,
+                              d_hidden, d, w.m.rows, c0, 0, s, (float*)w.dzt, w.Vpad * Tc / 2),
               fn);
     }
     if (nchunks == 0 && !accumulate_dw) RFT_HIP(launch_fill_zero(d_weight, V * d, s), fn);
@@ -834,12 +836,13 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
                                  lse, grad_logp, bonus ? w.ce : nullptr, w.cmu, w.dzt, s),
             fn);
     RFT_HIP(launch_transpose_blk(w.hc, d, cnt, c0, Tc, Tc, w.dpad, w.hct, s, w.Kp), fn);
-    RFT_HIP(mfma_gemm_store(w.dz, w.Vpad, w.wt, w.Vpad, Tc, d, w.Vpad, cnt, c0, Tc, 1, 0,
-                            d_hidden, d, w.m.rows, c0, 0, s, 1, 1),
-            fn);
     // dW = dZ^T . Hc with both operands K-contiguous (K = the chunk's rows)
     RFT_HIP(mfma_gemm_store(w.dzt, Tc, w.hct, Tc, V, d, Tc, cnt, c0, Tc, 0, 1, d_weight, d,
-                            nullptr, 0, (ci > 0 || accumulate_dw) ? 1 : 0, s, 1, 1),
+                            nullptr, 0, (ci > 0 || accumulate_dw) ? 1 : 0, s),
+            fn);
+    // dH; dZ^T is no longer needed and holds the partial sums where K is split
+    RFT_HIP(mfma_gemm_store(w.dz, w.Vpad, w.wt, w.Vpad, Tc, d, w.Vpad, cnt, c0, Tc, 1, 0,
+                            d_hidden, d, w.m.rows, c0, 0, s, (float*)w.dzt, w.Vpad * Tc / 2),
             fn);
   }
   if (nchunks == 0 && !accumulate_dw) RFT_HIP(launch_fill_zero(d_weight, V * d, s), fn);

@@ -322,7 +322,7 @@ hipError_t mfma_gemm_store(const uint16_t* A, int64_t lda, const uint16_t* B, in
                            int64_t M, int64_t N, int64_t K, const int32_t* cnt, int64_t cnt_off,
                            int64_t cnt_cap, int m_from_cnt, int k_from_cnt, float* C, int64_t ldc,
                            const int32_t* rows, int64_t rows_off, int accumulate, hipStream_t s,
-                           int a_blk = 0, int b_blk = 0);
+                           float* part = nullptr, int64_t part_elems = 0);
 // Compute units of the current device (cached per device).
 hipError_t cu_count(int* n);
 hipError_t f32_fwd_stats(const float* H, int64_t d, const float* W, int64_t V, const int32_t* rows,
