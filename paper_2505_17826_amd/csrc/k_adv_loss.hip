@@ -497,42 +497,26 @@ hipError_t launch_loss_fwd(const rft_tokens& tok, const TokMeta& m, const float*
 // Merge the per-vocabulary-tile partials (m, s, u) of each valid row into
 // lse, entropy = lse - u/s and logp = z_y - lse; masked rows get 0.
 // parts are [ntiles][ld] with the compacted row index as the inner index.
-__global__ void __launch_bounds__(256) k_merge_rows(
+__global__ void __launch_bounds__(kMergeThreads) k_merge_rows(
     const int32_t* __restrict__ kidx, const int32_t* __restrict__ ids, int64_t T, int64_t V,
     const float* __restrict__ pm, const float* __restrict__ ps, const float* __restrict__ pu,
     int ntiles, int64_t ld, const float* __restrict__ zy, float* __restrict__ logp,
     float* __restrict__ ent, float* __restrict__ lse) {
-  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  int k = kidx[t];
+  __shared__ LseSum sh[kMergeThreads];
+  const int64_t t = (int64_t)blockIdx.x * kMergeRows + threadIdx.x % kMergeRows;
+  const int k = t < T ? kidx[t] : -1;
+  const LseSum r = merge_tiles(pm + (k < 0 ? 0 : k), ps + (k < 0 ? 0 : k), pu + (k < 0 ? 0 : k), ld,
+                               ntiles, k >= 0, sh);
+  if (threadIdx.x >= kMergeRows || t >= T) return;
   if (k < 0) {
     logp[t] = 0.f;
     if (ent) ent[t] = 0.f;
     lse[t] = 0.f;
     return;
   }
-  float m = -INFINITY, sm = 0.f, u = 0.f;
-  // eight tiles' partials loaded ahead, merged in tile order
-  int j = 0;
-  for (; j + 8 <= ntiles; j += 8) {
-    float a[8], b[8], c[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int64_t o = (int64_t)(j + q) * ld + k;
-      a[q] = pm[o];
-      b[q] = ps[o];
-      c[q] = pu[o];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) lse_merge(m, sm, u, a[q], b[q], c[q]);
-  }
-  for (; j < ntiles; ++j) {
-    int64_t o = (int64_t)j * ld + k;
-    lse_merge(m, sm, u, pm[o], ps[o], pu[o]);
-  }
-  float L = m + logf(sm);
+  float L = r.m + logf(r.s);
   lse[t] = L;
-  if (ent) ent[t] = L - u / sm;
+  if (ent) ent[t] = L - r.u / r.s;
   int y = ids[t];
   logp[t] = (y >= 0 && (int64_t)y < V) ? zy[k] - L : __int_as_float(0x7fc00000);
 }
@@ -540,9 +524,9 @@ __global__ void __launch_bounds__(256) k_merge_rows(
 hipError_t launch_merge_rows(const rft_tokens& tok, const TokMeta& m, int64_t V, const float* pm,
                              const float* ps, const float* pu, int ntiles, int64_t ld,
                              const float* zy, float* logp, float* ent, float* lse, hipStream_t s) {
-  int nb = (int)((tok.T + 255) / 256);
+  const int64_t nb = (tok.T + kMergeRows - 1) / kMergeRows;
   if (nb > 0)
-    k_merge_rows<<<nb, 256, 0, s>>>(m.kidx, tok.token_ids, tok.T, V, pm, ps, pu, ntiles, ld, zy,
+    k_merge_rows<<<(unsigned)nb, kMergeThreads, 0, s>>>(m.kidx, tok.token_ids, tok.T, V, pm, ps, pu, ntiles, ld, zy,
                                     logp, ent, lse);
   return hipGetLastError();
 }

@@ -23,7 +23,7 @@
 
 namespace rft {
 
-__global__ void __launch_bounds__(256) k_step_rows(
+__global__ void __launch_bounds__(kMergeThreads) k_step_rows(
     const int32_t* __restrict__ rows, const int32_t* __restrict__ row_seq,
     const int32_t* __restrict__ n_i, const int32_t* __restrict__ meta,
     const int32_t* __restrict__ ids, int64_t V, int64_t c0, int64_t Tc,
@@ -32,29 +32,15 @@ __global__ void __launch_bounds__(256) k_step_rows(
     const float* __restrict__ ref, const float* __restrict__ adv, LossConst c,
     float* __restrict__ logp, float* __restrict__ ent, float* __restrict__ lse,
     float* __restrict__ grad, float* __restrict__ ce, float* __restrict__ cmu) {
-  const int64_t kl = (int64_t)blockIdx.x * 256 + threadIdx.x;  // row within the chunk
-  const int64_t k = c0 + kl;                                    // compacted row
-  if (kl >= Tc || k >= (int64_t)meta[0]) return;
+  __shared__ LseSum sh[kMergeThreads];
+  const int64_t kl = (int64_t)blockIdx.x * kMergeRows + threadIdx.x % kMergeRows;  // row within the chunk
+  const int64_t k = c0 + kl;                                                       // compacted row
+  const bool on = kl < Tc && k < (int64_t)meta[0];
+  const int64_t ko = on ? kl : 0;
+  const LseSum r = merge_tiles(pm + ko, ps + ko, pu + ko, Tc, ntiles, on, sh);
+  if (threadIdx.x >= kMergeRows || !on) return;
   const int t = rows[k];
-  float m = -INFINITY, sm = 0.f, u = 0.f;
-  // eight tiles' partials loaded ahead, merged in tile order
-  int j = 0;
-  for (; j + 8 <= ntiles; j += 8) {
-    float a[8], b[8], c[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int64_t o = (int64_t)(j + q) * Tc + kl;
-      a[q] = pm[o];
-      b[q] = ps[o];
-      c[q] = pu[o];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) lse_merge(m, sm, u, a[q], b[q], c[q]);
-  }
-  for (; j < ntiles; ++j) {
-    const int64_t o = (int64_t)j * Tc + kl;
-    lse_merge(m, sm, u, pm[o], ps[o], pu[o]);
-  }
+  const float m = r.m, sm = r.s, u = r.u;
   const float L = m + logf(sm);
   const float H = L - u / sm;
   lse[t] = L;
@@ -325,8 +311,8 @@ hipError_t launch_step_rows(const TokMeta& m, const int32_t* ids, int64_t V, int
                             int ntiles, const float* zy, const float* old, const float* ref,
                             const float* adv, const LossConst& c, float* logp, float* ent,
                             float* lse, float* grad, float* ce, float* cmu, hipStream_t s) {
-  const int nb = (int)((Tc + 255) / 256);
-  k_step_rows<<<nb, 256, 0, s>>>(m.rows, m.row_seq, m.n_i, m.meta, ids, V, c0, Tc, pm, ps, pu,
+  const int nb = (int)((Tc + kMergeRows - 1) / kMergeRows);
+  k_step_rows<<<nb, kMergeThreads, 0, s>>>(m.rows, m.row_seq, m.n_i, m.meta, ids, V, c0, Tc, pm, ps, pu,
                                  ntiles, zy, old, ref, adv, c, logp, ent, lse, grad, ce, cmu);
   return hipGetLastError();
 }
