@@ -8,9 +8,14 @@
 //           e_t the entropy-bonus coefficient, mu_t = lse - entropy) with
 //           non-temporal stores.
 // The fused kernel keeps the row on chip between the passes (registers, then
-// LDS) so that a row of up to about 600 KB is read from HBM once.  Every kernel
-// here gives each thread the same chunks of the row in the same order, so the
-// statistics-only, d_logits-only and fused kernels agree bit for bit.
+// LDS) so that a row of up to about 600 KB is read from HBM once; shorter rows
+// take variants with fewer registers and less LDS, several workgroups per CU,
+// so that one's loads run under another's stores.
+// A row is cut at the 16-byte boundaries of its logits (RowView): up to three
+// elements before the first, whole chunks of four, up to three after the last;
+// V and the base need no alignment.  Every kernel here gives each thread the
+// same chunks of the row in the same order, so the statistics-only,
+// d_logits-only and fused kernels agree bit for bit.
 #include "rft_internal.h"
 
 namespace rft {
@@ -18,6 +23,29 @@ namespace lg {
 
 constexpr int NT = 512;
 constexpr int UNROLL = 4;
+
+// d_logits need not share the logits' alignment
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// One row of V logits: h elements up to the first 16-byte boundary, n4 chunks
+// of four from there, tail elements after them.  Thread t < h + tail also
+// takes the single element extra(t).
+struct RowView {
+  const float* z4;  // first chunk
+  int64_t n4;
+  int h, tail;
+  __device__ __forceinline__ RowView(const float* z, int64_t V) {
+    const int a = (int)(((16 - ((uintptr_t)z & 15)) & 15) >> 2);
+    h = (int)(a < V ? a : V);
+    n4 = (V - h) >> 2;
+    tail = (int)((V - h) & 3);
+    z4 = z + h;
+  }
+  // row at a 16-byte boundary with V a multiple of 4
+  __device__ __forceinline__ RowView(const float* z, int64_t V, bool) : z4(z), n4(V >> 2), h(0), tail(0) {}
+  __device__ __forceinline__ bool has_extra(int t) const { return t < h + tail; }
+  __device__ __forceinline__ int64_t extra(int t) const { return t < h ? t : 4 * n4 + t; }
+};
 
 struct RowStats {
   float m, s, u;
@@ -79,65 +107,70 @@ __device__ RowStats block_stats(RowStats r, RowStats* sh) {
   return out;
 }
 
-template <bool VEC>
 __device__ RowStats row_pass1(const float* __restrict__ z, int64_t V, RowStats* sh) {
   RowStats r = {-INFINITY, 0.f, 0.f};
-  if (VEC) {
-    const float4* z4 = (const float4*)z;
-    int64_t n4 = V >> 2;
-    int64_t j = threadIdx.x;
-    for (; j + (UNROLL - 1) * NT < n4; j += UNROLL * NT) {
-      float4 q[UNROLL];
+  const RowView rv(z, V);
+  const float4* z4 = (const float4*)rv.z4;
+  int64_t j = threadIdx.x;
+  for (; j + (UNROLL - 1) * NT < rv.n4; j += UNROLL * NT) {
+    float4 q[UNROLL];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) q[u] = z4[j + u * NT];
+    for (int u = 0; u < UNROLL; ++u) q[u] = z4[j + u * NT];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) acc4(r, q[u]);
-    }
-    for (; j < n4; j += NT) acc4(r, z4[j]);
-  } else {
-    for (int64_t j = threadIdx.x; j < V; j += NT) acc1(r, z[j]);
+    for (int u = 0; u < UNROLL; ++u) acc4(r, q[u]);
   }
+  for (; j < rv.n4; j += NT) acc4(r, z4[j]);
+  if (rv.has_extra(threadIdx.x)) acc1(r, z[rv.extra(threadIdx.x)]);
   return block_stats(r, sh);
 }
 
-// d_logits of one row: c (onehot - p) + e p (z - mu) (dlogit), 16-byte stores.
-template <bool VEC>
+// d_logits of four logits, those of the chunk whose first element is j4 (from
+// the row's first chunk); ENT adds the entropy-bonus term e p (z - mu).
+template <bool ENT>
+__device__ __forceinline__ floatx4 dlogit4(floatx4 q, float lk, float c, float e, float mu,
+                                           int64_t j, int yc) {
+  const int hot = (yc >> 2) == j ? (yc & 3) : -1;
+  floatx4 d;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float p = __builtin_amdgcn_exp2f(fmaf(q[i], kLog2e, -lk));
+    d[i] = ENT ? dlogit(c, e, mu, p, q[i], hot == i) : c * ((hot == i ? 1.f : 0.f) - p);
+  }
+  return d;
+}
+template <bool ENT>
+__device__ __forceinline__ float dlogit1(float z, float lk, float c, float e, float mu, bool hot) {
+  const float p = __builtin_amdgcn_exp2f(fmaf(z, kLog2e, -lk));
+  return ENT ? dlogit(c, e, mu, p, z, hot) : c * ((hot ? 1.f : 0.f) - p);
+}
+
+// d_logits of one row: c (onehot - p) + e p (z - mu), 16-byte stores.
+template <bool ENT>
 __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, float c, float e,
                           float mu, int y, float* __restrict__ out) {
   const float lk = lse * kLog2e;
-  if (VEC) {
-    const float4* z4 = (const float4*)z;
-    floatx4* o4 = (floatx4*)out;
-    int64_t n4 = V >> 2;
-    for (int64_t j = threadIdx.x; j < n4; j += NT) {
-      float4 q = z4[j];
-      const int hot = (y >> 2) == j ? (y & 3) : -1;
-      floatx4 d;
-      d[0] = dlogit(c, e, mu, __builtin_amdgcn_exp2f(fmaf(q.x, kLog2e, -lk)), q.x, hot == 0);
-      d[1] = dlogit(c, e, mu, __builtin_amdgcn_exp2f(fmaf(q.y, kLog2e, -lk)), q.y, hot == 1);
-      d[2] = dlogit(c, e, mu, __builtin_amdgcn_exp2f(fmaf(q.z, kLog2e, -lk)), q.z, hot == 2);
-      d[3] = dlogit(c, e, mu, __builtin_amdgcn_exp2f(fmaf(q.w, kLog2e, -lk)), q.w, hot == 3);
-      __builtin_nontemporal_store(d, o4 + j);
-    }
-  } else {
-    for (int64_t j = threadIdx.x; j < V; j += NT)
-      out[j] = dlogit(c, e, mu, __builtin_amdgcn_exp2f(fmaf(z[j], kLog2e, -lk)), z[j], j == y);
+  const RowView rv(z, V);
+  const floatx4* z4 = (const floatx4*)rv.z4;
+  float* const o4 = out + rv.h;
+  const int yc = y - rv.h;
+  for (int64_t j = threadIdx.x; j < rv.n4; j += NT)
+    __builtin_nontemporal_store((f4u)dlogit4<ENT>(z4[j], lk, c, e, mu, j, yc), (f4u*)(o4 + 4 * j));
+  if (rv.has_extra(threadIdx.x)) {
+    const int64_t i = rv.extra(threadIdx.x);
+    out[i] = dlogit1<ENT>(z[i], lk, c, e, mu, i == y);
   }
 }
 
-template <bool VEC, int NTH = NT>
+// Zero a row of d_logits, 16-byte stores at its own boundaries.
 __device__ void zero_row(float* __restrict__ out, int64_t V) {
-  if (VEC) {
-    floatx4* o4 = (floatx4*)out;
-    floatx4 zz = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t j = threadIdx.x; j < (V >> 2); j += NTH) __builtin_nontemporal_store(zz, o4 + j);
-  } else {
-    for (int64_t j = threadIdx.x; j < V; j += NTH) out[j] = 0.f;
-  }
+  const RowView rv(out, V);
+  const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t j = threadIdx.x; j < rv.n4; j += NT)
+    __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
+  if (rv.has_extra(threadIdx.x)) out[rv.extra(threadIdx.x)] = 0.f;
 }
 
 // ---- statistics only (rft_token_logprobs_from_logits)
-template <bool VEC>
 __global__ void __launch_bounds__(NT) k_logits_stats(const float* __restrict__ logits, int64_t T,
                                                       int64_t V, const uint8_t* __restrict__ mask,
                                                       const int32_t* __restrict__ ids,
@@ -157,7 +190,7 @@ __global__ void __launch_bounds__(NT) k_logits_stats(const float* __restrict__ l
     return;
   }
   const float* z = logits + t * V;
-  RowStats r = row_pass1<VEC>(z, V, sh);
+  RowStats r = row_pass1(z, V, sh);
   if (threadIdx.x == 0) {
     float L = r.m + logf(r.s);
     int y = ids[t];
@@ -171,7 +204,7 @@ __global__ void __launch_bounds__(NT) k_logits_stats(const float* __restrict__ l
 }
 
 // ---- d_logits only (rft_ppo_clip_loss_bwd_logits)
-template <bool VEC>
+template <bool ENT>
 __global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ logits, int64_t T,
                                                     int64_t V, const uint8_t* __restrict__ mask,
                                                     const int32_t* __restrict__ ids,
@@ -183,17 +216,17 @@ __global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ log
   int64_t t = blockIdx.x;
   float* out = dl + t * V;
   if (!mask[t]) {
-    zero_row<VEC>(out, V);
+    zero_row(out, V);
     return;
   }
   int y = ids[t];
   const float L = lse[t];
-  const float e = egrad ? egrad[t] : 0.f, mu = egrad ? L - ent[t] : 0.f;
-  row_pass2<VEC>(logits + t * V, V, L, grad[t], e, mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
+  const float e = ENT ? egrad[t] : 0.f, mu = ENT ? L - ent[t] : 0.f;
+  row_pass2<ENT>(logits + t * V, V, L, grad[t], e, mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
 }
 
-// ---- fused: statistics, loss terms and d_logits (rft_ppo_clip_fused_logits)
-template <bool VEC>
+// ---- fused: statistics, loss terms and d_logits (rft_ppo_clip_fused_logits),
+// reading the row twice: rows beyond a buffer descriptor (V > 2^28)
 __global__ void __launch_bounds__(NT) k_logits_fused(
     const float* __restrict__ logits, int64_t T, int64_t V, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ ids, const int32_t* __restrict__ kidx,
@@ -202,15 +235,13 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
     const float* __restrict__ adv, LossConst cst, float* __restrict__ logp,
     float* __restrict__ ent, float* __restrict__ lse_out, float* __restrict__ grad_out,
     float* __restrict__ dl, LossPartial* __restrict__ parts) {
-  // (the launch also reserves dynamic LDS it does not use, to keep one
-  //  workgroup per CU)
   __shared__ RowStats sh[NT / 64 + 1];
   __shared__ float row_c, row_e, row_mu;
   int64_t t = blockIdx.x;
   float* out = dl + t * V;
   int k = kidx[t];
   if (k < 0) {
-    zero_row<VEC>(out, V);
+    zero_row(out, V);
     if (threadIdx.x == 0) {
       logp[t] = 0.f;
       if (ent) ent[t] = 0.f;
@@ -221,7 +252,7 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
     return;
   }
   const float* z = logits + t * V;
-  RowStats r = row_pass1<VEC>(z, V, sh);
+  RowStats r = row_pass1(z, V, sh);
   if (threadIdx.x == 0) {
     float L = r.m + logf(r.s);
     float H = L - r.u / r.s;
@@ -251,35 +282,14 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
   __syncthreads();
   float c = row_c, L = sh[NT / 64].m;
   int y = ids[t];
-  row_pass2<VEC>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
+  row_pass2<true>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
 }
 
 // ---- fused, with the row kept on chip: the first REG*NTC float4 of the row
 // stay in registers and the next LCAP float4 in LDS between the two passes;
 // only the remainder is read twice.
 typedef int v4i __attribute__((ext_vector_type(4)));
-constexpr int NTC = NT;                  // 2 waves per SIMD
-constexpr int REG = 56;                  // float4 per thread held in registers
-constexpr int REG_ENT = 54;              // the same with the entropy-bonus term (no spills)
-// float4 held in LDS (152 KiB): with the registers, rows of up to 153600
-// fp32 logits stay on chip (both vocabularies of the workloads)
-constexpr int LCAP = 19 * NTC;
-constexpr size_t kCachedLds = (size_t)LCAP * 16;
-static_assert(LCAP % NTC == 0, "every thread fills the same number of LDS slots");
-
-// d_logits of four logits; ENT adds the entropy-bonus term e p (z - mu)
-template <bool ENT>
-__device__ __forceinline__ floatx4 dlogit4(floatx4 q, float lk, float c, float e, float mu,
-                                           int64_t j, int y) {
-  const int hot = (y >> 2) == j ? (y & 3) : -1;
-  floatx4 d;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float p = __builtin_amdgcn_exp2f(fmaf(q[i], kLog2e, -lk));
-    d[i] = ENT ? dlogit(c, e, mu, p, q[i], hot == i) : c * ((hot == i ? 1.f : 0.f) - p);
-  }
-  return d;
-}
+constexpr int NTC = NT;
 
 __device__ __forceinline__ void acc4v(RowStats& r, floatx4 q) {
   acc4(r, make_float4(q[0], q[1], q[2], q[3]));
@@ -293,8 +303,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int64_
   return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, nr, 0x00020000);
 }
 
-template <bool ENT, int REGS>
-__global__ void __launch_bounds__(NTC) k_logits_fused_cached(
+// REGS float4 per thread in registers, LCH in LDS, WPS waves per SIMD (WPS / 2
+// workgroups per CU).  AL: every row of the logits and of d_logits starts at a
+// 16-byte boundary and V is a multiple of 4 (the general form costs the
+// one-workgroup variant 2.6%: 1848 us against 1800 for 8192 x 151936).
+template <bool ENT, int REGS, int LCH, int WPS, bool AL>
+__global__ void __launch_bounds__(NTC, WPS) k_logits_fused_cached(
     const float* __restrict__ logits, int64_t T, int64_t V, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ ids, const int32_t* __restrict__ kidx,
     const int32_t* __restrict__ row_seq, const int32_t* __restrict__ n_i,
@@ -302,6 +316,7 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
     const float* __restrict__ adv, LossConst cst, float* __restrict__ logp,
     float* __restrict__ ent, float* __restrict__ lse_out, float* __restrict__ grad_out,
     float* __restrict__ dl, LossPartial* __restrict__ parts) {
+  constexpr int LCAP = LCH * NTC;
   extern __shared__ floatx4 row_lds[];  // LCAP float4
   __shared__ RowStats sh[NTC / 64 + 1];
   __shared__ float row_c, row_e, row_mu;
@@ -309,16 +324,23 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
   const int64_t t = blockIdx.x;
   float* out = dl + t * V;
   const int k = kidx[t];
-  // one row is V * 4 bytes (at most 1 GiB, checked by the launcher)
-  const __amdgpu_buffer_rsrc_t rin = row_rsrc(logits + t * V, V * 4);
-  const __amdgpu_buffer_rsrc_t rout = row_rsrc(out, V * 4);
+  // descriptors over the row's whole chunks (at most 1 GiB, checked by the
+  // launcher)
+  const float* const zrow = logits + t * V;
+  const RowView rv = AL ? RowView(zrow, V, true) : RowView(zrow, V);
+  const int64_t n4 = rv.n4;
+  const __amdgpu_buffer_rsrc_t rin = row_rsrc(rv.z4, n4 * 16);
+  const __amdgpu_buffer_rsrc_t rout = row_rsrc(out + rv.h, n4 * 16);
   const uint32_t vo = (uint32_t)tid * 16u;
   constexpr uint32_t SU = (uint32_t)NTC * 16u;  // bytes between a thread's chunks
-  const int64_t n4 = V >> 2;
   if (k < 0) {
-    const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t j = tid, o = vo; j < n4; j += NTC, o += SU)
-      __builtin_amdgcn_raw_buffer_store_b128((v4i)zz, rout, (uint32_t)o, 0, 2);
+    if (AL) {
+      const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
+      for (int64_t j = tid, o = vo; j < n4; j += NTC, o += SU)
+        __builtin_amdgcn_raw_buffer_store_b128((v4i)zz, rout, (uint32_t)o, 0, 2);
+    } else {
+      zero_row(out, V);
+    }
     if (tid == 0) {
       logp[t] = 0.f;
       if (ent) ent[t] = 0.f;
@@ -332,7 +354,7 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
   // loads), issued now so that they have arrived when pass 1 ends.
   const int y0 = ids[t];
   const bool ok = y0 >= 0 && (int64_t)y0 < V;
-  const float zy = ok ? logits[t * V + y0] : 0.f;
+  const float zy = ok ? zrow[y0] : 0.f;
   const int i_seq = row_seq[k];
   const float old_t = old[t], ref_t = ref ? ref[t] : 0.f, adv_i = adv[i_seq];
   const int n_seq_i = n_i[i_seq];
@@ -376,6 +398,9 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
     acc4v(r, row_lds[s_]);
   for (int64_t j = j_rest + tid; j < n4; j += NTC)
     acc4v(r, (floatx4)__builtin_amdgcn_raw_buffer_load_b128(rin, (uint32_t)(j * 16), 0, 0));
+  const bool ex1 = rv.has_extra(tid);
+  const float zx = ex1 ? zrow[rv.extra(tid)] : 0.f;
+  if (ex1) acc1(r, zx);
   r = block_stats<NTC>(r, sh);
   if (tid == 0) {
     float L = r.m + logf(r.s);
@@ -404,7 +429,7 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
   }
   __syncthreads();
   const float c = row_c, lk = sh[NTC / 64].m * kLog2e, e = row_e, mu = row_mu;
-  const int y = ok ? y0 : -1;
+  const int y = (ok ? y0 : -1) - rv.h;  // from the row's first chunk
   // pass 2: same three regions; stores past the row are dropped by the descriptor
   uint32_t vo2 = vo;
   int nv2 = nv;
@@ -422,23 +447,19 @@ __global__ void __launch_bounds__(NTC) k_logits_fused_cached(
         (v4i)dlogit4<ENT>((floatx4)__builtin_amdgcn_raw_buffer_load_b128(rin, (uint32_t)(j * 16), 0, 0),
                      lk, c, e, mu, j, y),
         rout, (uint32_t)(j * 16), 0, 2);
+  if (rv.has_extra(tid)) {
+    const int64_t i = rv.extra(tid);
+    out[i] = dlogit1<ENT>(zrow[i], lk, c, e, mu, i - rv.h == y);
+  }
 }
 
 }  // namespace lg
 
-static bool vec_ok(const void* p, int64_t V) {
-  return (V % 4 == 0) && (((uintptr_t)p & 15) == 0);
-}
-
 hipError_t launch_logits_stats(const float* logits, const rft_tokens& tok, int64_t V, float* logp,
                                float* ent, float* lse, float* gathered, hipStream_t s) {
   if (tok.T <= 0) return hipSuccess;
-  if (vec_ok(logits, V))
-    lg::k_logits_stats<true><<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask,
-                                                                 tok.token_ids, logp, ent, lse, gathered);
-  else
-    lg::k_logits_stats<false><<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask,
-                                                                  tok.token_ids, logp, ent, lse, gathered);
+  lg::k_logits_stats<<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask, tok.token_ids,
+                                                        logp, ent, lse, gathered);
   return hipGetLastError();
 }
 
@@ -446,51 +467,67 @@ hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t
                              const float* lse, const float* grad, const float* egrad,
                              const float* ent, float* dl, hipStream_t s) {
   if (tok.T <= 0) return hipSuccess;
-  if (vec_ok(logits, V) && vec_ok(dl, V))
-    lg::k_logits_bwd<true><<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask,
-                                                               tok.token_ids, lse, grad, egrad,
-                                                               ent, dl);
-  else
-    lg::k_logits_bwd<false><<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask,
-                                                                tok.token_ids, lse, grad, egrad,
-                                                                ent, dl);
+  auto k = egrad ? lg::k_logits_bwd<true> : lg::k_logits_bwd<false>;
+  k<<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask, tok.token_ids, lse, grad, egrad,
+                                       ent, dl);
   return hipGetLastError();
 }
 
-constexpr size_t kFusedReserve = 96 * 1024;  // bytes of LDS reserved per workgroup
+// The on-chip variant for rows of V logits: the one with the most workgroups
+// per CU that holds the row (REGS + LCH chunks of four for each of 512
+// threads).  Two or more workgroups per CU overlap one row's loads with
+// another's stores, which one cannot: it has read its whole row before it
+// writes any of it.
+template <bool ENT, int REGS, int LCH, int WPS, bool AL, class... A>
+static hipError_t fused_cached(int64_t T, hipStream_t s, A... args) {
+  auto k = lg::k_logits_fused_cached<ENT, REGS, LCH, WPS, AL>;
+  constexpr int lds = LCH * lg::NTC * 16;
+  if (lds > 0) {
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  k<<<(unsigned)T, lg::NTC, lds, s>>>(args...);
+  return hipGetLastError();
+}
+template <bool ENT, bool AL, class... A>
+static hipError_t fused_any(int64_t V, int64_t T, hipStream_t s, A... args) {
+  constexpr int64_t kChunk = 4 * lg::NTC;  // logits per chunk of every thread
+  if (V <= 6 * kChunk) return fused_cached<ENT, 6, 0, 8, AL>(T, s, args...);
+  if (V <= 17 * kChunk) return fused_cached<ENT, 11, 6, 6, AL>(T, s, args...);
+  if (V <= 31 * kChunk) return fused_cached<ENT, 22, 9, 4, AL>(T, s, args...);
+  // 152 KiB of LDS: rows of up to 153600 logits stay on chip (149504 with the
+  // entropy bonus, whose term needs two chunks' registers); longer rows read
+  // their rest twice
+  return fused_cached<ENT, ENT ? 54 : 56, 19, 2, AL>(T, s, args...);
+}
 
 hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const TokMeta& m,
                                int64_t V, const float* old, const float* ref, const float* adv,
                                const LossConst& c, float* logp, float* ent, float* lse,
                                float* grad, float* dl, LossPartial* parts, LossPartial* parts2,
                                rft_ppo_stats* st, hipStream_t s) {
+  hipError_t e = hipSuccess;
   if (tok.T > 0) {
     // buffer descriptors span one row: 32-bit byte offsets
-    if (vec_ok(logits, V) && vec_ok(dl, V) && V <= ((int64_t)1 << 28)) {
-      const void* fn = c.ent_coef > 0.f ? (const void*)lg::k_logits_fused_cached<true, lg::REG_ENT>
-                                        : (const void*)lg::k_logits_fused_cached<false, lg::REG>;
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lg::kCachedLds);
-      if (e != hipSuccess) return e;
-      if (c.ent_coef > 0.f)
-        lg::k_logits_fused_cached<true, lg::REG_ENT><<<(unsigned)tok.T, lg::NTC, lg::kCachedLds, s>>>(
-            logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta, old, ref,
-            adv, c, logp, ent, lse, grad, dl, parts);
-      else
-        lg::k_logits_fused_cached<false, lg::REG><<<(unsigned)tok.T, lg::NTC, lg::kCachedLds, s>>>(
-            logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta, old, ref,
-            adv, c, logp, ent, lse, grad, dl, parts);
-    } else {
-      hipError_t e = hipFuncSetAttribute((const void*)lg::k_logits_fused<false>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)kFusedReserve);
-      if (e != hipSuccess) return e;
-      lg::k_logits_fused<false><<<(unsigned)tok.T, lg::NT, kFusedReserve, s>>>(
+    if (V > ((int64_t)1 << 28)) {
+      lg::k_logits_fused<<<(unsigned)tok.T, lg::NT, 0, s>>>(
           logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta, old, ref,
           adv, c, logp, ent, lse, grad, dl, parts);
+      e = hipGetLastError();
+    } else {
+      const bool al = V % 4 == 0 && (((uintptr_t)logits | (uintptr_t)dl) & 15) == 0;
+      auto go = [&](auto k) {
+        return k(V, tok.T, s, logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i,
+                 m.meta, old, ref, adv, c, logp, ent, lse, grad, dl, parts);
+      };
+      if (c.ent_coef > 0.f)
+        e = al ? go([](auto... a) { return fused_any<true, true>(a...); })
+               : go([](auto... a) { return fused_any<true, false>(a...); });
+      else
+        e = al ? go([](auto... a) { return fused_any<false, true>(a...); })
+               : go([](auto... a) { return fused_any<false, false>(a...); });
     }
   }
-  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // one partial per row: first reduced per 256-row block (fixed order), so
   // that the final single-workgroup sum reads T / 256 partials
