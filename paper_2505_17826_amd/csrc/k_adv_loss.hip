@@ -326,9 +326,31 @@ hipError_t launch_group_adv_ids(const float* r, const int32_t* gid, int64_t n, i
 }
 
 // -------------------------------------------------------- loss reduction ----
-__device__ void block_reduce_partial(LossPartial& p, LossPartial* out) {
-  __shared__ LossPartial sh[16];
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// The loss kernels run at most kLossBlocks blocks of kLossThreads threads, up to
+// kLossRows rows of a thread in flight at a time.  What bounds a loss call is
+// the chain of dependent steps (compaction index, rollout, its counts, the fp64
+// terms, the sums), not its bytes: few waves, since each pays for the eleven
+// sums, and few blocks, since each one's arrival at the final sum costs an L2
+// write-back (1024 blocks took 31 us).
+constexpr int kLossThreads = 256, kLossBlocks = 256, kLossRows = 4;
+static int loss_blocks(int64_t T) {
+  const int64_t nb = (T + kLossThreads - 1) / kLossThreads;
+  return (int)(nb < 1 ? 1 : (nb > kLossBlocks ? kLossBlocks : nb));
+}
+
+// The fields of a partial as eight doubles and three integers.
+constexpr int kFields = 11, kDoubles = 8;
+static_assert(sizeof(LossPartial) == kFields * 8 && sizeof(long long) == 8, "fields of 8 bytes");
+
+__device__ __forceinline__ void add_partial(LossPartial& p, const LossPartial& q) {
+  p.loss += q.loss; p.pg += q.pg; p.klw += q.klw; p.kl += q.kl;
+  p.ent += q.ent; p.ratio += q.ratio; p.sft += q.sft; p.entw += q.entw;
+  p.clipped += q.clipped; p.bad += q.bad; p.expert += q.expert;
+}
+
+// Sum over the block in a fixed order: thread f < kFields returns field f's bits.
+__device__ __forceinline__ long long block_total(LossPartial p, LossPartial* sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, f = threadIdx.x;
   p.loss = wave_sum_d(p.loss);
   p.pg = wave_sum_d(p.pg);
   p.klw = wave_sum_d(p.klw);
@@ -337,160 +359,192 @@ __device__ void block_reduce_partial(LossPartial& p, LossPartial* out) {
   p.ratio = wave_sum_d(p.ratio);
   p.sft = wave_sum_d(p.sft);
   p.entw = wave_sum_d(p.entw);
-  p.clipped = wave_sum_ll(p.clipped);
-  p.bad = wave_sum_ll(p.bad);
-  p.expert = wave_sum_ll(p.expert);
+  p.clipped = wave_sum_i((int)p.clipped);  // counts of at most T <= 2^30 rows
+  p.bad = wave_sum_i((int)p.bad);
+  p.expert = wave_sum_i((int)p.expert);
+  __syncthreads();  // sh may still be read from a previous sum
   if (lane == 0) sh[w] = p;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    LossPartial t = sh[0];
-    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) {
-      t.loss += sh[i].loss; t.pg += sh[i].pg; t.klw += sh[i].klw; t.kl += sh[i].kl;
-      t.ent += sh[i].ent; t.ratio += sh[i].ratio; t.sft += sh[i].sft; t.entw += sh[i].entw;
-      t.clipped += sh[i].clipped; t.bad += sh[i].bad; t.expert += sh[i].expert;
-    }
-    *out = t;
+  long long bits = 0;
+  if (f < kDoubles) {
+    double d = 0.0;
+    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) d += ((const double*)(sh + i))[f];
+    bits = __double_as_longlong(d);
+  } else if (f < kFields) {
+    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) bits += ((const long long*)(sh + i))[f];
   }
+  return bits;
 }
 
-// Per-token loss over rows [0, T): grid of 256-row blocks.
-__global__ void __launch_bounds__(256) k_loss_fwd(
-    const uint8_t* __restrict__ mask, const int32_t* __restrict__ ids, const int32_t* __restrict__ kidx,
-    const int32_t* __restrict__ row_seq, const int32_t* __restrict__ n_i, const int32_t* __restrict__ meta,
+__device__ void write_stats(const LossPartial& t, const int32_t* meta, rft_ppo_stats* st,
+                            int sft_only) {
+  const int N = meta[0], S = meta[1], Ne = meta[2], Ng = N - Ne;
+  const double inv = N > 0 ? 1.0 / (double)N : 0.0;
+  const double invg = Ng > 0 ? 1.0 / (double)Ng : 0.0;
+  st->loss = N > 0 ? t.loss : 0.0;
+  st->pg_loss = N > 0 ? t.pg : 0.0;
+  st->kl_loss = N > 0 ? t.klw : 0.0;
+  st->kl_mean = t.kl * invg;
+  st->entropy_mean = t.ent * inv;
+  st->ratio_mean = t.ratio * invg;
+  st->clipfrac = (double)t.clipped * invg;
+  st->n_valid = N;
+  st->n_seq_valid = S;
+  st->n_clipped = t.clipped;
+  st->n_bad_ids = t.bad;
+  st->sft_loss = sft_only ? (N > 0 ? t.loss : 0.0) : (Ne > 0 ? t.sft / (double)Ne : 0.0);
+  st->n_expert = Ne;
+  st->entropy_loss = N > 0 ? t.entw : 0.0;
+}
+
+// The stats from every block's partial (all threads of every block call this
+// last).  Each block's sum goes to parts[blockIdx.x]; the last block to arrive
+// (an atomic count, which launch_tokmeta has set to 0; the fences make every
+// block's sum visible to it) adds them in index order, so the result does not
+// depend on which block that is.  One launch of a single workgroup less (8-9 us).
+__device__ void reduce_stats(const LossPartial& p, LossPartial* parts, int32_t* meta,
+                             rft_ppo_stats* st, int sft_only) {
+  __shared__ LossPartial sh[kLossThreads / 64];
+  __shared__ LossPartial tot;
+  __shared__ int last;
+  const int f = threadIdx.x;
+  long long bits = block_total(p, sh);
+  if (gridDim.x > 1) {
+    if (f < kFields) {
+      ((long long*)(parts + blockIdx.x))[f] = bits;
+      __threadfence();
+    }
+    if (f == 0) last = atomicAdd(meta + kMetaCounter, 1) == (int)gridDim.x - 1 ? 1 : 0;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    LossPartial q = RFT_ZERO_PARTIAL;
+    if (f < (int)gridDim.x) q = parts[f];
+    bits = block_total(q, sh);
+  }
+  if (f < kFields) ((long long*)&tot)[f] = bits;
+  __syncthreads();
+  if (f == 0) write_stats(tot, meta, st, sft_only);
+}
+
+// Per-token loss over rows [0, T).
+__global__ void __launch_bounds__(kLossThreads) k_loss_fwd(
+    const int32_t* __restrict__ ids, const int32_t* __restrict__ kidx,
+    const int32_t* __restrict__ row_seq, const int32_t* __restrict__ n_i, int32_t* meta,
     int64_t T, const float* __restrict__ logp,
     const float* __restrict__ old, const float* __restrict__ ref, const float* __restrict__ adv,
     const float* __restrict__ ent, LossConst c, float* __restrict__ grad,
-    float* __restrict__ egrad, LossPartial* __restrict__ parts) {
-  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    float* __restrict__ egrad, LossPartial* parts, rft_ppo_stats* __restrict__ st) {
   LossPartial p = RFT_ZERO_PARTIAL;
-  if (t < T) {
-    int k = kidx[t];
-    float gout = 0.f, eout = 0.f;
-    if (k >= 0) {
-      int i = row_seq[k];
-      int y = ids[t];
-      if (y < 0 || (int64_t)y >= c.V) {
-        p.bad = 1;
-      } else {
-        float lp = logp[t];
-        float rf = ref ? ref[t] : lp;
-        const bool ex = c.is_expert && c.is_expert[i];
-        gout = row_loss(lp, old[t], rf, adv[i], n_i[i], ex, meta, ent ? (double)ent[t] : 0.0, c,
-                        p, &eout);
-      }
+  const int64_t step = (int64_t)gridDim.x * kLossThreads;
+  for (int64_t t0 = (int64_t)blockIdx.x * kLossThreads + threadIdx.x; t0 < T; t0 += kLossRows * step) {
+    int k[kLossRows], i[kLossRows], y[kLossRows], n[kLossRows];
+    float lp[kLossRows], od[kLossRows], rf[kLossRows], A[kLossRows], en[kLossRows];
+    bool ex[kLossRows];
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) {
+      const int64_t t = t0 + u * step;
+      k[u] = t < T ? kidx[t] : -1;
     }
-    grad[t] = gout;
-    if (egrad) egrad[t] = eout;
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) {
+      const int64_t t = k[u] < 0 ? t0 : t0 + u * step;
+      i[u] = k[u] < 0 ? 0 : row_seq[k[u]];
+      y[u] = ids[t];
+      lp[u] = logp[t];
+      od[u] = old[t];
+      rf[u] = ref ? ref[t] : lp[u];
+      en[u] = ent ? ent[t] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) {
+      n[u] = n_i[i[u]];
+      A[u] = adv[i[u]];
+      ex[u] = c.is_expert && c.is_expert[i[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kLossRows; ++u) {
+      const int64_t t = t0 + u * step;
+      if (t >= T) break;
+      float gout = 0.f, eout = 0.f;
+      if (k[u] >= 0) {
+        if (y[u] < 0 || (int64_t)y[u] >= c.V) {
+          p.bad += 1;
+        } else {
+          LossPartial q = RFT_ZERO_PARTIAL;
+          gout = row_loss(lp[u], od[u], rf[u], A[u], n[u], ex[u], meta, (double)en[u], c, q, &eout);
+          add_partial(p, q);
+        }
+      }
+      grad[t] = gout;
+      if (egrad) egrad[t] = eout;
+    }
   }
-  block_reduce_partial(p, parts + blockIdx.x);
+  reduce_stats(p, parts, meta, st, 0);
 }
 
-// One block: fixed-order sum of the block partials into the stats struct.
-__global__ void __launch_bounds__(1024) k_loss_final(const LossPartial* __restrict__ parts, int n,
-                                                     const int32_t* __restrict__ meta,
-                                                     rft_ppo_stats* __restrict__ st, int sft_only) {
+// Sum of per-row partials.
+__global__ void __launch_bounds__(kLossThreads) k_loss_reduce(const LossPartial* __restrict__ parts,
+                                                              int64_t n, LossPartial* out,
+                                                              int32_t* meta,
+                                                              rft_ppo_stats* __restrict__ st) {
   LossPartial p = RFT_ZERO_PARTIAL;
-  // each thread sums a contiguous run, in order
-  int per = (n + 1023) / 1024;
-  int a = threadIdx.x * per, b = min(n, a + per);
-  for (int i = a; i < b; ++i) {
-    p.loss += parts[i].loss; p.pg += parts[i].pg; p.klw += parts[i].klw; p.kl += parts[i].kl;
-    p.ent += parts[i].ent; p.ratio += parts[i].ratio; p.sft += parts[i].sft;
-    p.entw += parts[i].entw;
-    p.clipped += parts[i].clipped; p.bad += parts[i].bad; p.expert += parts[i].expert;
-  }
-  __shared__ LossPartial out;
-  block_reduce_partial(p, &out);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int N = meta[0], S = meta[1], Ne = meta[2], Ng = N - Ne;
-    const double inv = N > 0 ? 1.0 / (double)N : 0.0;
-    const double invg = Ng > 0 ? 1.0 / (double)Ng : 0.0;
-    st->loss = N > 0 ? out.loss : 0.0;
-    st->pg_loss = N > 0 ? out.pg : 0.0;
-    st->kl_loss = N > 0 ? out.klw : 0.0;
-    st->kl_mean = out.kl * invg;
-    st->entropy_mean = out.ent * inv;
-    st->ratio_mean = out.ratio * invg;
-    st->clipfrac = (double)out.clipped * invg;
-    st->n_valid = N;
-    st->n_seq_valid = S;
-    st->n_clipped = out.clipped;
-    st->n_bad_ids = out.bad;
-    st->sft_loss = sft_only ? st->loss : (Ne > 0 ? out.sft / (double)Ne : 0.0);
-    st->n_expert = Ne;
-    st->entropy_loss = N > 0 ? out.entw : 0.0;
-  }
+  for (int64_t i = (int64_t)blockIdx.x * kLossThreads + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kLossThreads)
+    add_partial(p, parts[i]);
+  reduce_stats(p, out, meta, st, 0);
 }
 
-hipError_t launch_loss_final(const LossPartial* parts, int nparts, const int32_t* meta,
-                             rft_ppo_stats* stats, hipStream_t s, int sft_only) {
-  k_loss_final<<<1, 1024, 0, s>>>(parts, nparts, meta, stats, sft_only);
-  return hipGetLastError();
-}
-
-__global__ void __launch_bounds__(256) k_loss_reduce256(const LossPartial* __restrict__ parts,
-                                                        int64_t n, LossPartial* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  LossPartial p = i < n ? parts[i] : RFT_ZERO_PARTIAL;
-  block_reduce_partial(p, out + blockIdx.x);
-}
-
-hipError_t launch_loss_reduce256(const LossPartial* parts, int64_t n, LossPartial* out,
-                                 hipStream_t s) {
-  if (n > 0) k_loss_reduce256<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(parts, n, out);
+hipError_t launch_loss_reduce(const LossPartial* parts, int64_t n, LossPartial* tmp, int32_t* meta,
+                              rft_ppo_stats* stats, hipStream_t s) {
+  k_loss_reduce<<<loss_blocks(n), kLossThreads, 0, s>>>(parts, n, tmp, meta, stats);
   return hipGetLastError();
 }
 
 // SFT loss of the train-only mode: sum_t w_t (-logp_t) over the valid rows
 // whose id is in range, w_t the aggregation weight; grad = -w_t.
-__global__ void __launch_bounds__(256) k_sft_fwd(
-    const uint8_t* __restrict__ mask, const int32_t* __restrict__ ids,
-    const int32_t* __restrict__ kidx, const int32_t* __restrict__ row_seq,
-    const int32_t* __restrict__ n_i, const int32_t* __restrict__ meta, int64_t T, int64_t V,
-    const float* __restrict__ logp, int agg, double denom, float* __restrict__ grad,
-    LossPartial* __restrict__ parts) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(kLossThreads) k_sft_fwd(
+    const int32_t* __restrict__ ids, const int32_t* __restrict__ kidx,
+    const int32_t* __restrict__ row_seq, const int32_t* __restrict__ n_i, int32_t* meta, int64_t T,
+    int64_t V, const float* __restrict__ logp, int agg, double denom, float* __restrict__ grad,
+    LossPartial* parts, rft_ppo_stats* __restrict__ st) {
   LossPartial p = RFT_ZERO_PARTIAL;
-  if (t < T) {
+  for (int64_t t = (int64_t)blockIdx.x * kLossThreads + threadIdx.x; t < T;
+       t += (int64_t)gridDim.x * kLossThreads) {
     const int k = kidx[t];
     float g = 0.f;
     if (k >= 0) {
       const int y = ids[t];
       if (y < 0 || (int64_t)y >= V) {
-        p.bad = 1;
+        p.bad += 1;
       } else {
         const double w = agg_weight(agg, denom, n_i[row_seq[k]], meta[0], meta[1]);
-        p.loss = w * -(double)logp[t];
+        p.loss += w * -(double)logp[t];
         g = (float)-w;
       }
     }
     grad[t] = g;
   }
-  block_reduce_partial(p, parts + blockIdx.x);
+  reduce_stats(p, parts, meta, st, 1);
 }
 
 hipError_t launch_sft_fwd(const rft_tokens& tok, const TokMeta& m, int64_t V, const float* logp,
                           int agg, double denom, float* grad, LossPartial* parts,
                           rft_ppo_stats* st, hipStream_t s) {
-  const int nb = (int)((tok.T + 255) / 256);
-  if (nb > 0)
-    k_sft_fwd<<<nb, 256, 0, s>>>(tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta, tok.T,
-                                 V, logp, agg, denom, grad, parts);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_loss_final(parts, nb, m.meta, st, s, 1);
+  k_sft_fwd<<<loss_blocks(tok.T), kLossThreads, 0, s>>>(tok.token_ids, m.kidx, m.row_seq, m.n_i,
+                                                        m.meta, tok.T, V, logp, agg, denom, grad,
+                                                        parts, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_loss_fwd(const rft_tokens& tok, const TokMeta& m, const float* logp,
                            const float* old, const float* ref, const float* adv, const float* ent,
                            const LossConst& c, float* grad, float* egrad, LossPartial* parts,
                            rft_ppo_stats* st, hipStream_t s) {
-  int nb = (int)((tok.T + 255) / 256);
-  if (nb > 0)
-    k_loss_fwd<<<nb, 256, 0, s>>>(tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta,
-                                  tok.T, logp, old, ref, adv, ent, c, grad, egrad, parts);
-  return launch_loss_final(parts, nb, m.meta, st, s);
+  k_loss_fwd<<<loss_blocks(tok.T), kLossThreads, 0, s>>>(tok.token_ids, m.kidx, m.row_seq, m.n_i,
+                                                         m.meta, tok.T, logp, old, ref, adv, ent, c,
+                                                         grad, egrad, parts, st);
+  return hipGetLastError();
 }
 
 // -------------------------------------------------------- lse partials ----

@@ -20,13 +20,20 @@ __global__ void __launch_bounds__(256) k_gather_rows16(const uint16_t* __restric
   }
 }
 
-// Zero the rows of out[T, width] whose mask is 0.
+// Zero the rows of out[T, width] whose mask is 0, and those rows' entries of up
+// to three per-token vectors.
 __global__ void __launch_bounds__(256) k_zero_masked_rows(const uint8_t* __restrict__ mask,
                                                           int64_t T, int64_t width,
-                                                          float* __restrict__ out) {
+                                                          float* __restrict__ out, float* v0,
+                                                          float* v1, float* v2) {
   for (int64_t t = blockIdx.x; t < T; t += gridDim.x) {
     if (mask[t]) continue;
     for (int64_t j = threadIdx.x; j < width; j += 256) out[t * width + j] = 0.f;
+    if (threadIdx.x == 0) {
+      if (v0) v0[t] = 0.f;
+      if (v1) v1[t] = 0.f;
+      if (v2) v2[t] = 0.f;
+    }
   }
 }
 
@@ -50,8 +57,9 @@ hipError_t launch_gather_rows16(const uint16_t* H, int64_t d, const int32_t* row
 }
 
 hipError_t launch_zero_masked_rows(const uint8_t* mask, int64_t T, int64_t width, float* out,
-                                   hipStream_t s) {
-  if (T > 0) k_zero_masked_rows<<<(unsigned)(T < 4096 ? T : 4096), 256, 0, s>>>(mask, T, width, out);
+                                   hipStream_t s, float* v0, float* v1, float* v2) {
+  if (T > 0)
+    k_zero_masked_rows<<<(unsigned)(T < 4096 ? T : 4096), 256, 0, s>>>(mask, T, width, out, v0, v1, v2);
   return hipGetLastError();
 }
 

@@ -529,10 +529,7 @@ hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const
     }
   }
   if (e != hipSuccess) return e;
-  // one partial per row: first reduced per 256-row block (fixed order), so
-  // that the final single-workgroup sum reads T / 256 partials
-  if ((e = launch_loss_reduce256(parts, tok.T, parts2, s)) != hipSuccess) return e;
-  return launch_loss_final(parts2, (int)((tok.T + 255) / 256), m.meta, st, s);
+  return launch_loss_reduce(parts, tok.T, parts2, m.meta, st, s);
 }
 
 }  // namespace rft

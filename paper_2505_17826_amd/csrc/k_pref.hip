@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(1024) k_dpo_pairs(
   __shared__ double shd[16];
   __shared__ long long shl[16];
   // each thread takes a contiguous run of pairs, in order
-  const int64_t per = (n_pairs + 1023) / 1024;
+  const int64_t per = (n_pairs + blockDim.x - 1) / blockDim.x;
   const int64_t k0 = (int64_t)threadIdx.x * per;
   const int64_t k1 = k0 + per < n_pairs ? k0 + per : n_pairs;
   long long cnt = 0, nbad = 0;
@@ -146,7 +146,8 @@ hipError_t launch_dpo(const rft_tokens& tok, const TokMeta& m, int64_t V, const 
     k_dpo_seq<<<(unsigned)tok.n_seq, kPrefT, 0, s>>>(tok.seq_start, tok.mask, tok.token_ids,
                                                      tok.T, V, logp, ref, w.pi, w.rho, w.bad,
                                                      seq_logp);
-  k_dpo_pairs<<<1, 1024, 0, s>>>(tok.n_seq / 2, m.n_i, m.meta, w.pi, w.rho, w.bad, (double)beta,
+  // one wave for few pairs: its block sums cost a barrier and an LDS round each
+  k_dpo_pairs<<<1, tok.n_seq <= 512 ? 64 : 1024, 0, s>>>(tok.n_seq / 2, m.n_i, m.meta, w.pi, w.rho, w.bad, (double)beta,
                                  (double)ls, w.coef, st);
   if (tok.T > 0)
     k_dpo_grad<<<(unsigned)((tok.T + 255) / 256), 256, 0, s>>>(m.kidx, m.row_seq, tok.token_ids,

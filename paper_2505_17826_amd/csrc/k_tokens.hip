@@ -1,7 +1,8 @@
 // Token bookkeeping: compaction of the masked rows (the "unpadding" a
 // training engine does before the model, Sec. 2.1.2) and per-rollout counts of
 // the tokens that enter the objective (action mask, Sec. 2.2 / Sec. 3.1.2).
-// Integer work, bit-exact and deterministic: block counts, one scan, scatter.
+// Integer work, bit-exact and deterministic: block counts and scatter (small
+// batches in one workgroup).
 #include "rft_internal.h"
 
 namespace rft {
@@ -10,6 +11,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kPerThread = kK0Rows / kThreads;  // 8 consecutive rows per thread
+static_assert(kPerThread == 8, "mask8 reads eight rows");
 
 __device__ int block_sum_int(int v, int* red) {
   int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -22,64 +24,183 @@ __device__ int block_sum_int(int v, int* red) {
   return t;
 }
 
-// Exclusive scan of one int per thread over a block of kThreads threads.
-__device__ int block_excl_scan(int v, int* sh) {
-  sh[threadIdx.x] = v;
+// Sums of three ints over the block (red3: three per wave), valid in thread 0.
+__device__ void block_sum3(int& a, int& b, int& c, int (*red3)[3]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  a = wave_sum_i(a);
+  b = wave_sum_i(b);
+  c = wave_sum_i(c);
+  if (lane == 0) red3[w][0] = a, red3[w][1] = b, red3[w][2] = c;
   __syncthreads();
-  for (int o = 1; o < kThreads; o <<= 1) {
-    int add = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += add;
-    __syncthreads();
+  if (threadIdx.x == 0)
+    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) {
+      a += red3[i][0];
+      b += red3[i][1];
+      c += red3[i][2];
+    }
+}
+
+// Exclusive scan of one int per thread over the block; *total gets the sum.
+__device__ int block_excl_scan(int v, int* red, int* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  int incl = sh[threadIdx.x];
+  if (lane == 63) red[w] = x;
   __syncthreads();
-  return incl - v;
-}
-
-__global__ void __launch_bounds__(kThreads) k_block_count(const uint8_t* __restrict__ mask,
-                                                          int64_t T, int32_t* __restrict__ blk) {
-  __shared__ int red[4];
-  int64_t r0 = (int64_t)blockIdx.x * kK0Rows;
-  int c = 0;
-  for (int j = threadIdx.x; j < kK0Rows; j += kThreads) {
-    int64_t t = r0 + j;
-    if (t < T && mask[t]) ++c;
+  int before = 0, all = 0;
+  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
+    before += i < w ? red[i] : 0;
+    all += red[i];
   }
-  c = block_sum_int(c, red);
-  if (threadIdx.x == 0) blk[blockIdx.x] = c;
+  __syncthreads();
+  *total = all;
+  return before + x - v;
 }
 
-__global__ void __launch_bounds__(kThreads) k_seq_count(const uint8_t* __restrict__ mask,
-                                                        const int32_t* __restrict__ ss,
-                                                        int64_t n_seq, int64_t T,
-                                                        int32_t* __restrict__ n_i) {
-  __shared__ int red[4];
-  int64_t i = blockIdx.x;
-  int64_t a = ss[i], b = ss[i + 1];
-  a = a < 0 ? 0 : (a > T ? T : a);
-  b = b < a ? a : (b > T ? T : b);
-  int c = 0;
-  for (int64_t t = a + threadIdx.x; t < b; t += kThreads) c += mask[t] ? 1 : 0;
-  c = block_sum_int(c, red);
-  if (threadIdx.x == 0) n_i[i] = c;
-}
-
-// One block: block counts -> exclusive offsets (in place), N and S.
-__global__ void __launch_bounds__(kThreads) k_scan(int32_t* __restrict__ blk, int nblk,
-                                                   const int32_t* __restrict__ n_i, int64_t n_seq,
-                                                   const uint8_t* __restrict__ is_expert,
-                                                   int32_t* __restrict__ meta) {
-  __shared__ int sh[kThreads];
-  __shared__ int red[4];
-  int carry = 0;
-  for (int b0 = 0; b0 < nblk; b0 += kThreads) {
-    int b = b0 + threadIdx.x;
-    int v = b < nblk ? blk[b] : 0;
-    int ex = block_excl_scan(v, sh);
-    if (b < nblk) blk[b] = carry + ex;
-    carry += block_sum_int(v, red);
+// Flags of the rows t0 .. t0 + 7 that enter the objective (bit j: row t0 + j).
+__device__ __forceinline__ uint32_t mask8(const uint8_t* __restrict__ mask, int64_t t0, int64_t T) {
+  uint32_t f = 0;
+  if (t0 + 8 <= T && ((uintptr_t)(mask + t0) & 7) == 0) {
+    const uint64_t w = *(const uint64_t*)(mask + t0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f |= ((w >> (8 * j)) & 0xff) ? 1u << j : 0u;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (t0 + j < T && mask[t0 + j]) f |= 1u << j;
   }
+  return f;
+}
+
+// The rows and rollout of the flagged rows t0 .. t0 + 7 from compacted index
+// off on; ss is seq_start (LDS or global).  The rollout of a row is the largest
+// i in [0, n_seq) with ss[i] <= t, searched for the first row and walked from
+// there (always in bounds).
+template <typename P>
+__device__ __forceinline__ void place8(uint32_t f, int64_t t0, int64_t T, P ss, int n_seq, int off,
+                                       int32_t* __restrict__ rows, int32_t* __restrict__ row_seq,
+                                       int32_t* __restrict__ kidx) {
+  int lo = 0, hi = n_seq - 1;
+  while (f && lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((int64_t)ss[mid] <= t0) lo = mid; else hi = mid - 1;
+  }
+  int64_t next = lo + 1 < n_seq ? (int64_t)ss[lo + 1] : T;  // first row of the next rollout
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int64_t t = t0 + j;
+    if (t >= T) break;
+    if (f >> j & 1) {
+      while (next <= t) {
+        ++lo;
+        next = lo + 1 < n_seq ? (int64_t)ss[lo + 1] : T;
+      }
+      rows[off] = (int32_t)t;
+      row_seq[off] = lo;
+      kidx[t] = off++;
+    } else {
+      kidx[t] = -1;
+    }
+  }
+}
+
+// Small batches: everything in one workgroup (prefix counts of the mask and the
+// rollouts' starts in LDS).  A call on few rows is a chain of launches of a few
+// microseconds each; the four that every path took were 15 us of the 67 of a
+// loss call on 128 rows, this one is 4.  Larger batches take two launches: 24 ->
+// 11 us at 262144 rows.
+constexpr int kSmallSeq = 2048;
+template <int NTH>
+__global__ void __launch_bounds__(NTH) k_tokmeta_small(const rft_tokens tok, TokMeta m) {
+  constexpr int kSmallT = 8 * NTH;
+  __shared__ int pre[kSmallT + 1];
+  __shared__ int ss[kSmallSeq + 1];
+  __shared__ int red[16];
+  const int T = (int)tok.T, n_seq = (int)tok.n_seq, tid = threadIdx.x;
+  for (int i = tid; i <= n_seq; i += NTH) ss[i] = tok.seq_start[i];
+  const int t0 = tid * 8;
+  const uint32_t f = t0 < T ? mask8(tok.mask, t0, T) : 0u;
+  int N;
+  const int off = block_excl_scan(__builtin_popcount(f), red, &N);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (t0 + j <= T) pre[t0 + j] = off + __builtin_popcount(f & ((1u << j) - 1));
+  if (tid == NTH - 1 && T == kSmallT) pre[T] = N;
+  __syncthreads();
+  int s = 0, ne = 0, se = 0;
+  for (int i = tid; i < n_seq; i += NTH) {
+    int a = ss[i], b = ss[i + 1];
+    a = a < 0 ? 0 : (a > T ? T : a);
+    b = b < a ? a : (b > T ? T : b);
+    const int n = pre[b] - pre[a];
+    m.n_i[i] = n;
+    s += n > 0 ? 1 : 0;
+    if (tok.is_expert && tok.is_expert[i]) {
+      ne += n;
+      se += n > 0 ? 1 : 0;
+    }
+  }
+  __shared__ int red3[16][3];
+  block_sum3(s, ne, se, red3);
+  if (tid == 0) {
+    m.meta[0] = N;
+    m.meta[1] = s;
+    m.meta[2] = ne;
+    m.meta[3] = se;
+    m.meta[kMetaCounter] = 0;
+  }
+  if (t0 < T) place8(f, t0, T, (const int*)ss, n_seq, off, m.rows, m.row_seq, m.kidx);
+}
+
+// Valid rows of [a, b): four mask bytes at a time between its 4-byte boundaries.
+__device__ __forceinline__ int count_range(const uint8_t* __restrict__ mask, int64_t a, int64_t b) {
+  const int64_t m0 = (int64_t)((uintptr_t)mask & 3);
+  int64_t a4 = ((a + m0 + 3) & ~(int64_t)3) - m0, b4 = ((b + m0) & ~(int64_t)3) - m0;
+  if (a4 > b) a4 = b;
+  if (b4 < a4) b4 = a4;
+  int c = 0;
+  for (int64_t t = a4 + (int64_t)threadIdx.x * 4; t < b4; t += kThreads * 4) {
+    const uint32_t w = *(const uint32_t*)(mask + t);
+    c += __builtin_popcount((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
+  }
+  if (a + threadIdx.x < a4) c += mask[a + threadIdx.x] ? 1 : 0;
+  if (b4 + threadIdx.x < b) c += mask[b4 + threadIdx.x] ? 1 : 0;
+  return c;
+}
+
+// Blocks [0, nblk): valid rows of each block of kK0Rows rows; the next n_seq
+// blocks: valid rows of each rollout.
+__global__ void __launch_bounds__(kThreads) k_count(const uint8_t* __restrict__ mask,
+                                                    const int32_t* __restrict__ ss, int64_t T,
+                                                    int64_t nblk, int32_t* __restrict__ blk,
+                                                    int32_t* __restrict__ n_i,
+                                                    int32_t* __restrict__ meta) {
+  __shared__ int red[4];
+  const int64_t b = blockIdx.x;
+  int64_t lo, hi;
+  if (b < nblk) {
+    lo = b * kK0Rows;
+    hi = lo + kK0Rows < T ? lo + kK0Rows : T;
+  } else {
+    lo = ss[b - nblk], hi = ss[b - nblk + 1];
+    lo = lo < 0 ? 0 : (lo > T ? T : lo);
+    hi = hi < lo ? lo : (hi > T ? T : hi);
+  }
+  const int c = block_sum_int(count_range(mask, lo, hi), red);
+  if (threadIdx.x == 0) {
+    if (b < nblk) blk[b] = c; else n_i[b - nblk] = c;
+    if (b == 0) meta[kMetaCounter] = 0;
+  }
+}
+
+// S, expert tokens and expert rollouts with tokens (all threads of one block).
+__device__ void seq_totals(const int32_t* __restrict__ n_i, int64_t n_seq,
+                           const uint8_t* __restrict__ is_expert, int N, int* red,
+                           int32_t* __restrict__ meta) {
   int s = 0, ne = 0, se = 0;
   for (int64_t i = threadIdx.x; i < n_seq; i += kThreads) {
     s += n_i[i] > 0 ? 1 : 0;
@@ -88,57 +209,53 @@ __global__ void __launch_bounds__(kThreads) k_scan(int32_t* __restrict__ blk, in
       se += n_i[i] > 0 ? 1 : 0;
     }
   }
-  s = block_sum_int(s, red);
-  ne = block_sum_int(ne, red);
-  se = block_sum_int(se, red);
+  __shared__ int red3[16][3];
+  block_sum3(s, ne, se, red3);
   if (threadIdx.x == 0) {
-    meta[0] = carry;
+    meta[0] = N;
     meta[1] = s;
     meta[2] = ne;
     meta[3] = se;
   }
 }
 
-__device__ __forceinline__ int seq_of(const int32_t* __restrict__ ss, int64_t n_seq, int64_t t) {
-  // largest i in [0, n_seq-1] with ss[i] <= t (clamped, always in bounds)
-  int lo = 0, hi = (int)n_seq - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if ((int64_t)ss[mid] <= t) lo = mid; else hi = mid - 1;
+// One block: block counts -> exclusive offsets (in place), N and S (batches of
+// more than kSelfBlocks blocks; in smaller ones each block of k_scatter adds the
+// counts before it itself, one launch less).
+constexpr int64_t kSelfBlocks = 1024;
+__global__ void __launch_bounds__(kThreads) k_scan(int32_t* __restrict__ blk, int nblk,
+                                                   const int32_t* __restrict__ n_i, int64_t n_seq,
+                                                   const uint8_t* __restrict__ is_expert,
+                                                   int32_t* __restrict__ meta) {
+  __shared__ int red[4];
+  int carry = 0;
+  for (int b0 = 0; b0 < nblk; b0 += kThreads) {
+    int b = b0 + threadIdx.x, total;
+    int ex = block_excl_scan(b < nblk ? blk[b] : 0, red, &total);
+    if (b < nblk) blk[b] = carry + ex;
+    carry += total;
   }
-  return lo;
+  seq_totals(n_i, n_seq, is_expert, carry, red, meta);
 }
 
-__global__ void __launch_bounds__(kThreads) k_scatter(const uint8_t* __restrict__ mask,
-                                                      const int32_t* __restrict__ ss, int64_t n_seq,
-                                                      int64_t T, const int32_t* __restrict__ blk,
-                                                      int32_t* __restrict__ rows,
-                                                      int32_t* __restrict__ row_seq,
-                                                      int32_t* __restrict__ kidx) {
-  __shared__ int sh[kThreads];
-  int64_t r0 = (int64_t)blockIdx.x * kK0Rows + (int64_t)threadIdx.x * kPerThread;
-  uint8_t f[kPerThread];
-  int c = 0;
-#pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
-    int64_t t = r0 + j;
-    f[j] = (t < T && mask[t]) ? 1 : 0;
-    c += f[j];
+template <bool SCANNED>
+__global__ void __launch_bounds__(kThreads) k_scatter(const rft_tokens tok, TokMeta m, int nblk) {
+  __shared__ int red[4];
+  int base;
+  if (SCANNED) {
+    base = m.blk[blockIdx.x];
+  } else {
+    int v = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kThreads) v += m.blk[b];
+    base = block_sum_int(v, red);
+    if ((int)blockIdx.x == nblk - 1)  // base + its own count = N
+      seq_totals(m.n_i, tok.n_seq, tok.is_expert, base + m.blk[blockIdx.x], red, m.meta);
   }
-  int off = blk[blockIdx.x] + block_excl_scan(c, sh);
-#pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
-    int64_t t = r0 + j;
-    if (t >= T) break;
-    if (f[j]) {
-      rows[off] = (int32_t)t;
-      row_seq[off] = seq_of(ss, n_seq, t);
-      kidx[t] = off;
-      ++off;
-    } else {
-      kidx[t] = -1;
-    }
-  }
+  const int64_t t0 = (int64_t)blockIdx.x * kK0Rows + (int64_t)threadIdx.x * kPerThread;
+  const uint32_t f = t0 < tok.T ? mask8(tok.mask, t0, tok.T) : 0u;
+  int total;
+  const int off = base + block_excl_scan(__builtin_popcount(f), red, &total);
+  place8(f, t0, tok.T, tok.seq_start, (int)tok.n_seq, off, m.rows, m.row_seq, m.kidx);
 }
 
 }  // namespace
@@ -151,19 +268,27 @@ TokMeta carve_tokmeta(Carver& c, int64_t T, int64_t n_seq) {
   m.kidx = c.take<int32_t>(T > 0 ? T : 1);
   m.n_i = c.take<int32_t>(n_seq > 0 ? n_seq : 1);
   m.blk = c.take<int32_t>(nblk > 0 ? nblk : 1);
-  m.meta = c.take<int32_t>(4);
+  m.meta = c.take<int32_t>(kMetaCounter + 1);
   return m;
 }
 
 hipError_t launch_tokmeta(const rft_tokens& tok, const TokMeta& m, hipStream_t s) {
-  int64_t T = tok.T, n_seq = tok.n_seq;
-  int nblk = (int)((T + kK0Rows - 1) / kK0Rows);
-  if (nblk > 0) k_block_count<<<nblk, kThreads, 0, s>>>(tok.mask, T, m.blk);
-  if (n_seq > 0) k_seq_count<<<(unsigned)n_seq, kThreads, 0, s>>>(tok.mask, tok.seq_start, n_seq, T, m.n_i);
-  k_scan<<<1, kThreads, 0, s>>>(m.blk, nblk, m.n_i, n_seq, tok.is_expert, m.meta);
-  if (nblk > 0 && n_seq > 0)
-    k_scatter<<<nblk, kThreads, 0, s>>>(tok.mask, tok.seq_start, n_seq, T, m.blk, m.rows,
-                                        m.row_seq, m.kidx);
+  const int64_t T = tok.T, n_seq = tok.n_seq;
+  if (T <= 8192 && n_seq <= kSmallSeq) {
+    if (T <= 2048) k_tokmeta_small<256><<<1, 256, 0, s>>>(tok, m);
+    else k_tokmeta_small<1024><<<1, 1024, 0, s>>>(tok, m);
+    return hipGetLastError();
+  }
+  const int64_t nblk = (T + kK0Rows - 1) / kK0Rows;
+  if (nblk + n_seq > 0)
+    k_count<<<(unsigned)(nblk + n_seq), kThreads, 0, s>>>(tok.mask, tok.seq_start, T, nblk, m.blk,
+                                                          m.n_i, m.meta);
+  if (nblk == 0 || nblk > kSelfBlocks)
+    k_scan<<<1, kThreads, 0, s>>>(m.blk, (int)nblk, m.n_i, n_seq, tok.is_expert, m.meta);
+  if (nblk > kSelfBlocks)
+    k_scatter<true><<<(unsigned)nblk, kThreads, 0, s>>>(tok, m, (int)nblk);
+  else if (nblk > 0)
+    k_scatter<false><<<(unsigned)nblk, kThreads, 0, s>>>(tok, m, (int)nblk);
   return hipGetLastError();
 }
 

@@ -587,11 +587,13 @@ rft_status rft_token_logprobs_from_logits(const rft_tokens* tok, const float* lo
   return RFT_OK;
 }
 
-rft_status rft_ppo_clip_loss_fwd(const rft_tokens* tok, int64_t V, const float* logp,
-                                 const float* old_logp, const float* ref_logp, const float* adv,
-                                 const float* entropy, const rft_ppo_params* params,
-                                 float* grad_logp, float* grad_entropy, rft_ppo_stats* stats,
-                                 void* ws, size_t ws_bytes, void* stream) {
+// have_meta (here and in loss_bwd): the token bookkeeping at the front of the
+// workspace is already there (the fp32 step, whose three calls share it).
+static rft_status loss_fwd(const rft_tokens* tok, int64_t V, const float* logp,
+                           const float* old_logp, const float* ref_logp, const float* adv,
+                           const float* entropy, const rft_ppo_params* params, float* grad_logp,
+                           float* grad_entropy, rft_ppo_stats* stats, void* ws, size_t ws_bytes,
+                           void* stream, bool have_meta) {
   const char* fn = "rft_ppo_clip_loss_fwd";
   rft_status st = check_tokens(tok, fn);
   if (st) return st;
@@ -608,7 +610,7 @@ rft_status rft_ppo_clip_loss_fwd(const rft_tokens* tok, int64_t V, const float* 
   if ((st = check_ws(fn, ws, ws_bytes, w.bytes))) return st;
   w = carve_loss(ws, *tok, false);
   hipStream_t s = (hipStream_t)stream;
-  RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
+  if (!have_meta) RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   LossConst c = loss_const(params, V, *tok);
   RFT_HIP(launch_loss_fwd(*tok, w.m, logp, old_logp, ref_logp,
                           adv, entropy, c, grad_logp, grad_entropy, w.parts, stats, s),
@@ -616,11 +618,20 @@ rft_status rft_ppo_clip_loss_fwd(const rft_tokens* tok, int64_t V, const float* 
   return RFT_OK;
 }
 
-rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, const void* weight,
-                                 int dtype, int64_t d, int64_t V, const float* lse,
-                                 const float* grad_logp, const float* grad_entropy,
-                                 const float* entropy, float* d_hidden, float* d_weight,
-                                 int32_t accumulate_dw, void* ws, size_t ws_bytes, void* stream) {
+rft_status rft_ppo_clip_loss_fwd(const rft_tokens* tok, int64_t V, const float* logp,
+                                 const float* old_logp, const float* ref_logp, const float* adv,
+                                 const float* entropy, const rft_ppo_params* params,
+                                 float* grad_logp, float* grad_entropy, rft_ppo_stats* stats,
+                                 void* ws, size_t ws_bytes, void* stream) {
+  return loss_fwd(tok, V, logp, old_logp, ref_logp, adv, entropy, params, grad_logp, grad_entropy,
+                  stats, ws, ws_bytes, stream, false);
+}
+
+static rft_status loss_bwd(const rft_tokens* tok, const void* hidden, const void* weight, int dtype,
+                           int64_t d, int64_t V, const float* lse, const float* grad_logp,
+                           const float* grad_entropy, const float* entropy, float* d_hidden,
+                           float* d_weight, int32_t accumulate_dw, void* ws, size_t ws_bytes,
+                           void* stream, bool have_meta) {
   const char* fn = "rft_ppo_clip_loss_bwd";
   rft_status st = check_tokens(tok, fn);
   if (st) return st;
@@ -637,7 +648,7 @@ rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, cons
   BwdWs w = carve_bwd(ws, *tok, d, V, dtype, Tc);
   hipStream_t s = (hipStream_t)stream;
   const int64_t T = tok->T;
-  RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
+  if (!have_meta) RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   if (T > 0) {
     RFT_HIP(launch_zero_masked_rows(tok->mask, T, d, d_hidden, s), fn);
   }
@@ -688,6 +699,15 @@ rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, cons
     if (nchunks == 0 && !accumulate_dw) RFT_HIP(launch_fill_zero(d_weight, V * d, s), fn);
   }
   return RFT_OK;
+}
+
+rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, const void* weight,
+                                 int dtype, int64_t d, int64_t V, const float* lse,
+                                 const float* grad_logp, const float* grad_entropy,
+                                 const float* entropy, float* d_hidden, float* d_weight,
+                                 int32_t accumulate_dw, void* ws, size_t ws_bytes, void* stream) {
+  return loss_bwd(tok, hidden, weight, dtype, d, V, lse, grad_logp, grad_entropy, entropy, d_hidden,
+                  d_weight, accumulate_dw, ws, ws_bytes, stream, false);
 }
 
 rft_status rft_ppo_clip_loss_bwd_logits(const rft_tokens* tok, const float* logits, int64_t V,
@@ -793,12 +813,13 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
     if ((st = rft_token_logprobs(tok, hidden, weight, dtype, d, V, logp, entropy, lse, ws,
                                  (size_t)front, stream)))
       return st;
-    if ((st = rft_ppo_clip_loss_fwd(tok, V, logp, old_logp, ref, adv, entropy, params, grad_logp,
-                                    egrad, stats, ws, (size_t)front, stream)))
+    const bool have_meta = tok->T > 0;  // rft_token_logprobs enqueues nothing without rows
+    if ((st = loss_fwd(tok, V, logp, old_logp, ref, adv, entropy, params, grad_logp, egrad, stats,
+                       ws, (size_t)front, stream, have_meta)))
       return st;
-    return rft_ppo_clip_loss_bwd(tok, hidden, weight, dtype, d, V, lse, grad_logp, egrad,
-                                 bonus ? entropy : nullptr, d_hidden, d_weight, accumulate_dw, ws,
-                                 (size_t)front, stream);
+    return loss_bwd(tok, hidden, weight, dtype, d, V, lse, grad_logp, egrad,
+                    bonus ? entropy : nullptr, d_hidden, d_weight, accumulate_dw, ws,
+                    (size_t)front, stream, have_meta);
   }
   if ((st = check_ws(fn, ws, ws_bytes, carve_step(nullptr, *tok, d, V, kBf16Align).bytes)))
     return st;
@@ -814,11 +835,9 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
   const int32_t* cnt = w.m.meta;
   RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   if (T > 0) {
-    RFT_HIP(launch_zero_masked_rows(tok->mask, T, d, d_hidden, s), fn);
-    // masked rows of the per-token outputs are 0; the chunks fill the valid rows
-    RFT_HIP(launch_fill_zero(logp, T, s), fn);
-    RFT_HIP(launch_fill_zero(lse, T, s), fn);
-    if (entropy) RFT_HIP(launch_fill_zero(entropy, T, s), fn);
+    // masked rows of d_hidden and of the per-token outputs are 0; the chunks
+    // fill the valid rows
+    RFT_HIP(launch_zero_masked_rows(tok->mask, T, d, d_hidden, s, logp, lse, entropy), fn);
     RFT_HIP(launch_rows_to_blk(H, d, w.m.rows, cnt, T, w.Kp, w.hc, s), fn);
     RFT_HIP(launch_rows_to_blk(W, d, nullptr, nullptr, V, w.Kp, w.wb, s), fn);
     RFT_HIP(launch_transpose_blk(W, d, nullptr, 0, V, w.Vpad, w.dpad, w.wt, s), fn);

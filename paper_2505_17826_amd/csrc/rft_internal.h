@@ -64,11 +64,26 @@ __device__ __forceinline__ void row16_sum_n(float (&v)[N]) {
   for (int e = 0; e < N; ++e) v[e] += dpp_f<0x140>(v[e]);
 }
 
-// Whole-wave (64 lanes) reductions via cross-lane shuffles.
+// Whole-wave (64 lanes) reductions.  Doubles go by DPP moves within rows of 16
+// lanes and scalar reads of the four rows' sums: eleven such sums by LDS
+// shuffles (two per double and step) cost a block of 16 waves 5 us.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const int2 b = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(b.x, CTRL, 0xF, 0xF, true),
+                                              __builtin_amdgcn_mov_dpp(b.y, CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ double lane_d(double v, int lane) {
+  const int2 b = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(b.x, lane),
+                                              __builtin_amdgcn_readlane(b.y, lane)));
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_d<0xB1>(v);
+  v += dpp_d<0x4E>(v);
+  v += dpp_d<0x141>(v);
+  v += dpp_d<0x140>(v);
+  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
 __device__ __forceinline__ float wave_sum_f(float v) {
 #pragma unroll
@@ -85,15 +100,13 @@ __device__ __forceinline__ float wave_min_f(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
   return v;
 }
-__device__ __forceinline__ long long wave_sum_ll(long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 __device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);
+  return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
+         __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
 // Merge of two online log-sum-exp partials (m: max, s: sum exp(z - m),
@@ -179,8 +192,10 @@ struct TokMeta {
   int32_t* kidx;     // [T]  compacted index of row t, -1 if masked
   int32_t* n_i;      // [n_seq] valid tokens per rollout
   int32_t* blk;      // [nblk] per-block counts, then offsets
-  int32_t* meta;     // [4]  N, S, expert tokens, expert rollouts with tokens
+  int32_t* meta;     // [5]  N, S, expert tokens, expert rollouts with tokens, and
+                     //      the block counter of the loss reduction (0 after launch_tokmeta)
 };
+constexpr int kMetaCounter = 4;
 
 struct Carver {
   char* base;
@@ -310,11 +325,11 @@ __device__ __forceinline__ float dlogit(float c, float e, float mu, float p, flo
 
 #define RFT_ZERO_PARTIAL LossPartial{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}
 
-hipError_t launch_loss_final(const LossPartial* parts, int nparts, const int32_t* meta,
-                             rft_ppo_stats* stats, hipStream_t s, int sft_only = 0);
-// out[b] = the fixed-order sum of parts[256 b .. 256 b + 255] (n parts)
-hipError_t launch_loss_reduce256(const LossPartial* parts, int64_t n, LossPartial* out,
-                                 hipStream_t s);
+// Fixed-order sum of n partials into *stats; tmp holds ceil(n / 256) partials
+// (one per block).
+// The counter meta[kMetaCounter] must be 0 (one such sum per launch_tokmeta).
+hipError_t launch_loss_reduce(const LossPartial* parts, int64_t n, LossPartial* tmp, int32_t* meta,
+                              rft_ppo_stats* stats, hipStream_t s);
 hipError_t launch_sft_fwd(const rft_tokens& tok, const TokMeta& m, int64_t V, const float* logp,
                           int agg, double denom, float* grad, LossPartial* parts,
                           rft_ppo_stats* st, hipStream_t s);
@@ -403,7 +418,8 @@ hipError_t launch_gather_rows16(const uint16_t* H, int64_t d, const int32_t* row
                                 const int32_t* cnt, int64_t cap, uint16_t* Hc, hipStream_t s);
 hipError_t launch_fill_zero(float* out, int64_t n, hipStream_t s);
 hipError_t launch_zero_masked_rows(const uint8_t* mask, int64_t T, int64_t width, float* out,
-                                   hipStream_t s);
+                                   hipStream_t s, float* v0 = nullptr, float* v1 = nullptr,
+                                   float* v2 = nullptr);
 hipError_t launch_logits_stats(const float* logits, const rft_tokens& tok, int64_t V, float* logp,
                                float* ent, float* lse, float* gathered, hipStream_t s);
 hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t V,

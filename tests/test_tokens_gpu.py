@@ -1,0 +1,65 @@
+"""Token bookkeeping at the edges of its paths: one workgroup (up to 8192 rows
+and 2048 rollouts), one block of 2048 rows more or less, the counts added by
+each block or scanned (past 2^21 rows), loss sums of one block, of many and of
+more than the last block adds; masks at odd addresses, empty rollouts, expert
+flags.  Counts are exact; the loss is the fp64 mean over valid tokens of values
+that are exact in fp32, so only its rounding order differs (1e-12 relative)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_17826_amd as R
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+CASES = [(1, 1), (7, 3), (256, 8), (257, 300), (2048, 2049), (8191, 5), (8192, 2048), (8193, 7),
+         (10240, 2049), (300001, 400), (700000, 33), ((1 << 21) + 5, 4099)]
+
+
+@pytest.mark.parametrize("shift", [0, 3])
+@pytest.mark.parametrize("T,n_seq", CASES)
+def test_counts_and_loss_sums(T, n_seq, shift):
+    print(f"[tokens] T={T} n_seq={n_seq} shift={shift}", flush=True)
+    r = np.random.default_rng(T + n_seq)
+    cuts = np.sort(r.integers(0, T + 1, size=n_seq - 1))  # some rollouts are empty
+    start = np.concatenate([[0], cuts, [T]]).astype(np.int32)
+    mask = (r.random(T) < 0.6).astype(np.uint8) * r.integers(1, 256, size=T).astype(np.uint8)
+    expert = (r.random(n_seq) < 0.3).astype(np.uint8)
+    ids = r.integers(0, 50, size=T).astype(np.int32)
+    bad = r.random(T) < 0.01
+    ids[bad] = 50
+    lp = -(r.integers(1, 64, size=T) / 8.0).astype(np.float32)
+    buf = torch.empty(T + 8, dtype=torch.uint8, device=DEV)
+    m = buf[shift:shift + T]
+    m.copy_(torch.from_numpy(mask))
+    t = lambda x: torch.from_numpy(x).to(DEV)  # noqa: E731
+    tok = R.Tokens(t(start), m, t(ids), t(expert))
+    grad, st = R.rft_ppo_clip_loss_fwd(tok, 50, t(lp), t(lp), None, torch.ones(n_seq, device=DEV),
+                                       R.ppo_params(0.2, 0.2, 0.0, 1, mix_mu=0.5))
+    s = R.stats_to_dict(st)
+    sg, sst = R.rft_sft_loss_fwd(tok, 50, t(lp), agg=0)
+    ss = R.stats_to_dict(sst)
+    v = mask != 0
+    seq = np.searchsorted(start[1:], np.arange(T), side="right")
+    n_i = np.bincount(seq[v], minlength=n_seq)
+    ex = expert[seq] != 0
+    N, S, Ne = int(v.sum()), int((n_i > 0).sum()), int((v & ex).sum())
+    for d in (s, ss):
+        assert (d["n_valid"], d["n_seq_valid"], d["n_bad_ids"]) == (N, S, int((v & bad).sum()))
+    assert s["n_expert"] == Ne
+    use = v & ~bad
+    Ng = N - Ne
+    g = np.zeros(T)
+    if Ng:
+        g[use & ~ex] = -0.5 / Ng
+    if Ne:
+        g[use & ex] = -0.5 / Ne
+    assert np.array_equal(grad.cpu().numpy(), g.astype(np.float32))
+    sft = -lp[use & ex].astype(np.float64).sum() / max(Ne, 1)
+    assert abs(s["sft_loss"] - sft) <= 1e-12 * abs(sft)
+    w = np.zeros(T)
+    w[use] = 1.0 / (S * n_i[seq[use]].astype(np.float64))
+    assert np.array_equal(sg.cpu().numpy(), (-w).astype(np.float32))
+    want = (w * -lp.astype(np.float64)).sum()
+    assert abs(ss["loss"] - want) <= 1e-12 * max(want, 1e-300)
