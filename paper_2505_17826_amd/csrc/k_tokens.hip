@@ -90,10 +90,11 @@ __device__ __forceinline__ void place8(uint32_t f, int64_t t0, int64_t T, P ss, 
     if ((int64_t)ss[mid] <= t0) lo = mid; else hi = mid - 1;
   }
   int64_t next = lo + 1 < n_seq ? (int64_t)ss[lo + 1] : T;  // first row of the next rollout
+  int kx[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int64_t t = t0 + j;
-    if (t >= T) break;
+    kx[j] = -1;
     if (f >> j & 1) {
       while (next <= t) {
         ++lo;
@@ -101,10 +102,17 @@ __device__ __forceinline__ void place8(uint32_t f, int64_t t0, int64_t T, P ss, 
       }
       rows[off] = (int32_t)t;
       row_seq[off] = lo;
-      kidx[t] = off++;
-    } else {
-      kidx[t] = -1;
+      kx[j] = off++;
     }
+  }
+  // kidx and t0 are multiples of 16 bytes and of 8 rows
+  if (t0 + 8 <= T) {
+    *(int4*)(kidx + t0) = make_int4(kx[0], kx[1], kx[2], kx[3]);
+    *(int4*)(kidx + t0 + 4) = make_int4(kx[4], kx[5], kx[6], kx[7]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (t0 + j < T) kidx[t0 + j] = kx[j];
   }
 }
 
@@ -238,9 +246,18 @@ __global__ void __launch_bounds__(kThreads) k_scan(int32_t* __restrict__ blk, in
   seq_totals(n_i, n_seq, is_expert, carry, red, meta);
 }
 
+// The rollouts' starts go to LDS where they fit: the search for a row's rollout
+// is a chain of dependent reads.
 template <bool SCANNED>
 __global__ void __launch_bounds__(kThreads) k_scatter(const rft_tokens tok, TokMeta m, int nblk) {
   __shared__ int red[4];
+  __shared__ int ss[kSmallSeq + 1];
+  const int n_seq = (int)tok.n_seq;
+  const bool inlds = n_seq <= kSmallSeq;
+  if (inlds)
+    for (int i = threadIdx.x; i <= n_seq; i += kThreads) ss[i] = tok.seq_start[i];
+  const int64_t t0 = (int64_t)blockIdx.x * kK0Rows + (int64_t)threadIdx.x * kPerThread;
+  const uint32_t f = t0 < tok.T ? mask8(tok.mask, t0, tok.T) : 0u;
   int base;
   if (SCANNED) {
     base = m.blk[blockIdx.x];
@@ -251,11 +268,11 @@ __global__ void __launch_bounds__(kThreads) k_scatter(const rft_tokens tok, TokM
     if ((int)blockIdx.x == nblk - 1)  // base + its own count = N
       seq_totals(m.n_i, tok.n_seq, tok.is_expert, base + m.blk[blockIdx.x], red, m.meta);
   }
-  const int64_t t0 = (int64_t)blockIdx.x * kK0Rows + (int64_t)threadIdx.x * kPerThread;
-  const uint32_t f = t0 < tok.T ? mask8(tok.mask, t0, tok.T) : 0u;
   int total;
   const int off = base + block_excl_scan(__builtin_popcount(f), red, &total);
-  place8(f, t0, tok.T, tok.seq_start, (int)tok.n_seq, off, m.rows, m.row_seq, m.kidx);
+  __syncthreads();
+  if (inlds) place8(f, t0, tok.T, (const int*)ss, n_seq, off, m.rows, m.row_seq, m.kidx);
+  else place8(f, t0, tok.T, tok.seq_start, n_seq, off, m.rows, m.row_seq, m.kidx);
 }
 
 }  // namespace

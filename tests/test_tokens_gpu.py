@@ -63,3 +63,30 @@ def test_counts_and_loss_sums(T, n_seq, shift):
     assert np.array_equal(sg.cpu().numpy(), (-w).astype(np.float32))
     want = (w * -lp.astype(np.float64)).sum()
     assert abs(ss["loss"] - want) <= 1e-12 * max(want, 1e-300)
+
+
+@pytest.mark.parametrize("mode", [R.RFT_ADV_GRPO, R.RFT_ADV_MEAN_CENTER, R.RFT_ADV_LEAVE_ONE_OUT])
+@pytest.mark.parametrize("n,n_groups", [(1, 1), (3, 2), (256, 300), (257, 31), (1023, 1), (1024, 64),
+                                        (1025, 64)])
+def test_advantages_of_few_rollouts(n, n_groups, mode):
+    """One launch up to 1024 rollouts, the bucketed path past them: fp64 sums
+    rounded once to fp32 (2^-24 of the result; 1e-12 for the sums' order)."""
+    r = np.random.default_rng(7 * n + mode)
+    rew = r.random(n).astype(np.float32)
+    rew[r.random(n) < 0.3] = 1.0
+    gid = r.integers(-1, n_groups + 1, size=n).astype(np.int32)
+    got = R.rft_group_advantages_ids(torch.from_numpy(rew).to(DEV), torch.from_numpy(gid).to(DEV),
+                                     n_groups, mode).cpu().numpy()
+    want = np.zeros(n)
+    for g in range(n_groups):
+        k = gid == g
+        v = rew[k].astype(np.float64)
+        if v.size < 2 or (mode == R.RFT_ADV_GRPO and v.min() == v.max()):
+            continue
+        if mode == R.RFT_ADV_GRPO:
+            want[k] = (v - v.mean()) / (v.std(ddof=1) + float(np.float32(1e-6)))
+        elif mode == R.RFT_ADV_MEAN_CENTER:
+            want[k] = v - v.mean()
+        else:
+            want[k] = v - (v.sum() - v) / (v.size - 1)
+    assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want) + 1e-12).all()
