@@ -156,16 +156,20 @@ __device__ __forceinline__ int pick_slices(int M, int N, int K, int ncu, int64_t
 }
 
 // Item b of an S-sliced M x N result: XCD b % 8 takes a contiguous run of
-// (slice, tile) items, tiles of one slice together, so the tiles that run on
-// one XCD read the same K range of both operands through its L2.
+// (slice, tile) items, the tiles of a slice in bands of kBand M-tiles walked
+// along N, so the 32 tiles that run on one XCD read the same K range of about
+// six panels of each operand through its L2.
+constexpr int kBand = 6;
 __device__ __forceinline__ bool slice_of(int b, int nTm, int nTn, int S, int& sl, int& mt, int& nt) {
   const int items = nTm * nTn * S, per = (items + 7) / 8;
   const int i = (b & 7) * per + (b >> 3);
   if ((b >> 3) >= per || i >= items) return false;
   sl = i / (nTm * nTn);
   const int t = i - sl * (nTm * nTn);
-  mt = t % nTm;
-  nt = t / nTm;
+  const int band = t / (kBand * nTn), r = t - band * (kBand * nTn);
+  const int gm = min(kBand, nTm - band * kBand);
+  mt = band * kBand + r % gm;
+  nt = r / gm;
   return true;
 }
 
@@ -1189,25 +1193,25 @@ hipError_t mfma_fwd_stats_blk(const uint16_t* Hb, int64_t d, const uint16_t* Wb,
 }
 
 // Forward of one chunk of compacted rows [c0, c0 + Tc) for the fused step:
-// Hc and W tile-blocked with Kp = d rounded up to 64 (c0 and Tc multiples of
-// 256); partials [ntiles][Tc] indexed by the chunk row, zy by the compacted
+// Hc tile-blocked with Kp = d rounded up to 64, W likewise or (w_blk = 0) as the
+// caller's row-major [V, d] (c0 and Tc multiples of 256); partials [ntiles][Tc] indexed by the chunk row, zy by the compacted
 // row, and y = z - (row maximum over the tile) in fp16 into y [Tc, Vpad]:
 // each 256 x 256 tile in the 128 KiB the tile-blocked layout gives it,
 // column-major.
-hipError_t mfma_fwd_stats_y(const uint16_t* Hc, int64_t d, const uint16_t* W, int64_t V,
-                            int64_t Vpad, const int32_t* rows, const int32_t* ids,
+hipError_t mfma_fwd_stats_y(const uint16_t* Hc, int64_t d, const uint16_t* W, bool w_blk,
+                            int64_t V, int64_t Vpad, const int32_t* rows, const int32_t* ids,
                             const int32_t* cnt, int64_t c0, int64_t Tc, float* pm, float* ps,
                             float* pu, float* zy, uint16_t* y, hipStream_t s) {
   const int64_t Kp = (d + 63) / 64 * 64;
   mf::Args a = {};
   a.A = Hc + c0 * Kp; a.lda = Kp; a.a_blk = 1;
-  a.B = W; a.ldb = Kp; a.b_blk = 1;
+  a.B = W; a.ldb = w_blk ? Kp : d; a.b_blk = w_blk;
   a.M = (int)Tc; a.N = (int)V; a.K = (int)d;
   a.cnt = cnt; a.cnt_off = c0; a.cnt_cap = Tc; a.m_from_cnt = 1;
   a.rows = rows; a.rows_off = c0; a.ids = ids;
   a.pm = pm; a.ps = ps; a.pu = pu; a.ldp = Tc; a.zy = zy; a.p_off = 0;
   a.y = y; a.ldy = Vpad;
-  if (fits384(Kp, Kp, d, 0)) {
+  if (w_blk && fits384(Kp, Kp, d, 0)) {
     mf::k_gemm384<mf::EPI_STATS_Y><<<grid_for384<mf::EPI_STATS_Y>(Tc, V), mf::NT, 0, s>>>(a);
     return hipGetLastError();
   }

@@ -140,6 +140,12 @@ struct FwdWs {
   size_t bytes;
 };
 bool fwd_blocked_ok(int dtype, int64_t d) { return dtype == RFT_BF16 && mfma_fwd_blk_ok(d); }
+// Whether the forward GEMM of T rows reads a tile-blocked copy of W: the copy
+// (440 us at d = 3584, V = 152064) is worth its cost from about 6600 valid rows
+// on, where the blocked operand and the 384-row tile save as much (6% of the
+// GEMM); both sides scale with V d.  T stands for the rows, of which about 60%
+// are valid in a padded batch.  The results are the same bit for bit.
+constexpr int64_t kBlockedWRows = 10240;
 // blocked: the bf16 forward from tile-blocked copies of the compacted rows
 // [round_up(T, 256), d] and of W [Vpad, d] (d a multiple of 64), for the
 // 384 x 256 GEMM tile; the copy of W adds Vpad d 2 bytes.
@@ -540,7 +546,7 @@ rft_status rft_token_logprobs(const rft_tokens* tok, const void* hidden, const v
   FwdWs w = carve_fwd(nullptr, *tok, d, V, dtype);
   if ((st = check_ws(fn, ws, ws_bytes, w.bytes))) return st;
   // a workspace that also holds the tile-blocked copies selects that path
-  const bool blocked = fwd_blocked_ok(dtype, d) &&
+  const bool blocked = fwd_blocked_ok(dtype, d) && tok->T > kBlockedWRows &&
                        ws_bytes >= carve_fwd(nullptr, *tok, d, V, dtype, true).bytes;
   w = carve_fwd(ws, *tok, d, V, dtype, blocked);
   hipStream_t s = (hipStream_t)stream;
@@ -833,18 +839,19 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
   const uint16_t* W = (const uint16_t*)weight;
   const int64_t nchunks = T > 0 ? (T + Tc - 1) / Tc : 0;
   const int32_t* cnt = w.m.meta;
+  const bool blockedW = T > kBlockedWRows;
   RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   if (T > 0) {
     // masked rows of d_hidden and of the per-token outputs are 0; the chunks
     // fill the valid rows
     RFT_HIP(launch_zero_masked_rows(tok->mask, T, d, d_hidden, s, logp, lse, entropy), fn);
     RFT_HIP(launch_rows_to_blk(H, d, w.m.rows, cnt, T, w.Kp, w.hc, s), fn);
-    RFT_HIP(launch_rows_to_blk(W, d, nullptr, nullptr, V, w.Kp, w.wb, s), fn);
+    if (blockedW) RFT_HIP(launch_rows_to_blk(W, d, nullptr, nullptr, V, w.Kp, w.wb, s), fn);
     RFT_HIP(launch_transpose_blk(W, d, nullptr, 0, V, w.Vpad, w.dpad, w.wt, s), fn);
   }
   for (int64_t ci = 0; ci < nchunks; ++ci) {
     const int64_t c0 = ci * Tc;
-    RFT_HIP(mfma_fwd_stats_y(w.hc, d, w.wb, V, w.Vpad, w.m.rows, tok->token_ids, cnt, c0, Tc, w.pm,
+    RFT_HIP(mfma_fwd_stats_y(w.hc, d, blockedW ? w.wb : W, blockedW, V, w.Vpad, w.m.rows, tok->token_ids, cnt, c0, Tc, w.pm,
                              w.ps, w.pu, w.zy, w.dz, s),
             fn);
     RFT_HIP(launch_step_rows(w.m, tok->token_ids, V, c0, Tc, w.pm, w.ps, w.pu, w.ntiles, w.zy,
