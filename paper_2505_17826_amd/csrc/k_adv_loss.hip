@@ -2,6 +2,7 @@
 // their fixed-order fp64 reduction, and the merge of the per-tile
 // log-sum-exp partials into per-token log-prob / entropy / lse.
 #include "rft_internal.h"
+#include "tokens_device.h"
 
 namespace rft {
 
@@ -570,6 +571,67 @@ hipError_t launch_loss_reduce(const LossPartial* parts, int64_t n, LossPartial* 
   return hipGetLastError();
 }
 
+// A handful of rows (at most kLossThreads) whose statistics are in P parts each:
+// the token bookkeeping, the merge, the row terms and the loss statistics in one
+// workgroup.  Every part is read before the terms (lse, c, e, entropy, [T] each)
+// take its place.
+template <int P>
+__global__ void __launch_bounds__(kLossThreads) k_few_terms(
+    const float* __restrict__ logits, const rft_tokens tok, TokMeta m, int64_t V,
+    const float* __restrict__ old, const float* __restrict__ ref, const float* __restrict__ adv,
+    LossConst c, float* __restrict__ logp, float* __restrict__ ent, float* __restrict__ lse,
+    float* __restrict__ grad, float* scratch, rft_ppo_stats* __restrict__ st) {
+  const int t = threadIdx.x, T = (int)tok.T;
+  const bool on = t < T && tok.mask[t];
+  RowStats v[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+    v[i] = on ? ((const RowStats*)scratch)[t * P + i] : RowStats{0.f, 1.f, 0.f};
+  int y = on ? tok.token_ids[t] : -1;
+  const bool ok = y >= 0 && (int64_t)y < V;
+  const float zy = ok ? logits[(int64_t)t * V + y] : 0.f;
+  const float od = on ? old[t] : 0.f, rf0 = on && ref ? ref[t] : 0.f;
+  tokmeta_small<kLossThreads>(tok, m);
+  __syncthreads();
+  LossPartial p = RFT_ZERO_PARTIAL;
+  if (t < T) {
+    float L = 0.f, H = 0.f, lp = 0.f, g = 0.f, e = 0.f;
+    if (on) {
+      tree_merge(v);
+      L = v[0].m + logf(v[0].s);
+      H = L - v[0].u / v[0].s;
+      lp = ok ? zy - L : __int_as_float(0x7fc00000);
+      if (!ok) {
+        p.bad = 1;
+      } else {
+        const int i = m.row_seq[m.kidx[t]];
+        const bool ex = c.is_expert && c.is_expert[i];
+        g = row_loss(lp, od, ref ? rf0 : lp, adv[i], m.n_i[i], ex, m.meta, (double)H, c, p, &e);
+      }
+    }
+    logp[t] = lp;
+    if (ent) ent[t] = H;
+    if (lse) lse[t] = L;
+    if (grad) grad[t] = g;
+    scratch[t] = L;
+    scratch[T + t] = g;
+    scratch[2 * T + t] = e;
+    scratch[3 * T + t] = H;
+  }
+  reduce_stats(p, nullptr, m.meta, st, 0);
+}
+
+hipError_t launch_few_terms(const float* logits, const rft_tokens& tok, const TokMeta& m, int64_t V,
+                            int P, const float* old, const float* ref, const float* adv,
+                            const LossConst& c, float* logp, float* ent, float* lse, float* grad,
+                            void* scratch, rft_ppo_stats* st, hipStream_t s) {
+  if (tok.T > kLossThreads) return hipErrorInvalidValue;
+  auto k = P == 8 ? k_few_terms<8> : P == 4 ? k_few_terms<4> : k_few_terms<2>;
+  k<<<1, kLossThreads, 0, s>>>(logits, tok, m, V, old, ref, adv, c, logp, ent, lse, grad,
+                               (float*)scratch, st);
+  return hipGetLastError();
+}
+
 // SFT loss of the train-only mode: sum_t w_t (-logp_t) over the valid rows
 // whose id is in range, w_t the aggregation weight; grad = -w_t.
 __global__ void __launch_bounds__(kLossThreads) k_sft_fwd(
@@ -625,10 +687,10 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_rows(
     const float* __restrict__ pm, const float* __restrict__ ps, const float* __restrict__ pu,
     int ntiles, int64_t ld, const float* __restrict__ zy, float* __restrict__ logp,
     float* __restrict__ ent, float* __restrict__ lse) {
-  __shared__ LseSum sh[kMergeThreads];
+  __shared__ RowStats sh[kMergeThreads];
   const int64_t t = (int64_t)blockIdx.x * kMergeRows + threadIdx.x % kMergeRows;
   const int k = t < T ? kidx[t] : -1;
-  const LseSum r = merge_tiles(pm + (k < 0 ? 0 : k), ps + (k < 0 ? 0 : k), pu + (k < 0 ? 0 : k), ld,
+  const RowStats r = merge_tiles(pm + (k < 0 ? 0 : k), ps + (k < 0 ? 0 : k), pu + (k < 0 ? 0 : k), ld,
                                ntiles, k >= 0, sh);
   if (threadIdx.x >= kMergeRows || t >= T) return;
   if (k < 0) {

@@ -47,9 +47,6 @@ struct RowView {
   __device__ __forceinline__ int64_t extra(int t) const { return t < h ? t : 4 * n4 + t; }
 };
 
-struct RowStats {
-  float m, s, u;
-};
 
 // Online (max, sum exp, sum exp * z) over a thread's logits.  Every exponent
 // argument is <= 0 (hardware exp2; results below 2^-126 flush to 0).  Logits
@@ -87,7 +84,9 @@ __device__ __forceinline__ void acc1(RowStats& r, float z) {
   r.u += e * zfin(z);
 }
 
-// Workgroup reduction of the per-thread online partials, in a fixed order.
+// Workgroup reduction of the per-thread online partials, in a fixed order: a
+// binary tree over the waves, so that a row cut into 2, 4 or 8 parts of whole
+// waves (k_logits_part) ends with the same bits.
 template <int NTH = NT>
 __device__ RowStats block_stats(RowStats r, RowStats* sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -97,9 +96,11 @@ __device__ RowStats block_stats(RowStats r, RowStats* sh) {
   if (lane == 0) sh[w] = RowStats{M, s, u};
   __syncthreads();
   if (threadIdx.x == 0) {
-    float m = -INFINITY, ss = 0.f, uu = 0.f;
-    for (int i = 0; i < NTH / 64; ++i) lse_merge(m, ss, uu, sh[i].m, sh[i].s, sh[i].u);
-    sh[NTH / 64] = RowStats{m, ss, uu};
+    RowStats v[NTH / 64];
+#pragma unroll
+    for (int i = 0; i < NTH / 64; ++i) v[i] = sh[i];
+    tree_merge(v);
+    sh[NTH / 64] = v[0];
   }
   __syncthreads();
   RowStats out = sh[NTH / 64];
@@ -144,30 +145,42 @@ __device__ __forceinline__ float dlogit1(float z, float lk, float c, float e, fl
   return ENT ? dlogit(c, e, mu, p, z, hot) : c * ((hot ? 1.f : 0.f) - p);
 }
 
-// d_logits of one row: c (onehot - p) + e p (z - mu), 16-byte stores.
+// d_logits of one row: c (onehot - p) + e p (z - mu), 16-byte stores; vt: the
+// thread's place among the row's NT threads.
 template <bool ENT>
 __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, float c, float e,
-                          float mu, int y, float* __restrict__ out) {
+                          float mu, int y, float* __restrict__ out, int vt) {
   const float lk = lse * kLog2e;
   const RowView rv(z, V);
   const floatx4* z4 = (const floatx4*)rv.z4;
   float* const o4 = out + rv.h;
   const int yc = y - rv.h;
-  for (int64_t j = threadIdx.x; j < rv.n4; j += NT)
+  // eight chunks' loads in flight at a time
+  constexpr int UN = 8;
+  int64_t j = vt;
+  for (; j + (UN - 1) * NT < rv.n4; j += UN * NT) {
+    floatx4 q[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) q[u] = z4[j + u * NT];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      __builtin_nontemporal_store((f4u)dlogit4<ENT>(q[u], lk, c, e, mu, j + u * NT, yc),
+                                  (f4u*)(o4 + 4 * (j + u * NT)));
+  }
+  for (; j < rv.n4; j += NT)
     __builtin_nontemporal_store((f4u)dlogit4<ENT>(z4[j], lk, c, e, mu, j, yc), (f4u*)(o4 + 4 * j));
-  if (rv.has_extra(threadIdx.x)) {
-    const int64_t i = rv.extra(threadIdx.x);
+  if (rv.has_extra(vt)) {
+    const int64_t i = rv.extra(vt);
     out[i] = dlogit1<ENT>(z[i], lk, c, e, mu, i == y);
   }
 }
 
 // Zero a row of d_logits, 16-byte stores at its own boundaries.
-__device__ void zero_row(float* __restrict__ out, int64_t V) {
+__device__ void zero_row(float* __restrict__ out, int64_t V, int vt) {
   const RowView rv(out, V);
   const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t j = threadIdx.x; j < rv.n4; j += NT)
-    __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
-  if (rv.has_extra(threadIdx.x)) out[rv.extra(threadIdx.x)] = 0.f;
+  for (int64_t j = vt; j < rv.n4; j += NT) __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
+  if (rv.has_extra(vt)) out[rv.extra(vt)] = 0.f;
 }
 
 // ---- statistics only (rft_token_logprobs_from_logits)
@@ -203,26 +216,67 @@ __global__ void __launch_bounds__(NT) k_logits_stats(const float* __restrict__ l
   }
 }
 
-// ---- d_logits only (rft_ppo_clip_loss_bwd_logits)
+// ---- d_logits only (rft_ppo_clip_loss_bwd_logits); 2^lp workgroups per row, of
+// NT / 2^lp threads each
 template <bool ENT>
-__global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ logits, int64_t T,
-                                                    int64_t V, const uint8_t* __restrict__ mask,
+__global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ logits, int64_t V,
+                                                    const uint8_t* __restrict__ mask,
                                                     const int32_t* __restrict__ ids,
                                                     const float* __restrict__ lse,
                                                     const float* __restrict__ grad,
                                                     const float* __restrict__ egrad,
                                                     const float* __restrict__ ent,
-                                                    float* __restrict__ dl) {
-  int64_t t = blockIdx.x;
+                                                    float* __restrict__ dl, int lp) {
+  const int64_t t = blockIdx.x >> lp;
+  const int vt = (int)(blockIdx.x & ((1u << lp) - 1)) * (NT >> lp) + threadIdx.x;
   float* out = dl + t * V;
   if (!mask[t]) {
-    zero_row(out, V);
+    zero_row(out, V, vt);
     return;
   }
   int y = ids[t];
   const float L = lse[t];
   const float e = ENT ? egrad[t] : 0.f, mu = ENT ? L - ent[t] : 0.f;
-  row_pass2<ENT>(logits + t * V, V, L, grad[t], e, mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
+  row_pass2<ENT>(logits + t * V, V, L, grad[t], e, mu, (y >= 0 && (int64_t)y < V) ? y : -1, out, vt);
+}
+
+// ---- a handful of long rows: one workgroup per row leaves CUs idle, and a CU
+// reads a row at its own rate (about 40 us for 600 KB read and written), so a
+// row is cut into P = 2, 4 or 8 parts of 8 / P waves: this kernel, the row terms
+// of all rows in one workgroup (launch_few_terms), then k_logits_bwd with P
+// workgroups per row, which finds the logits in the last-level cache.  Whole
+// call at V = 151936: 128 rows 47 -> 45 us, 64 rows 48 -> 36, 16 rows 46 -> 29.
+template <int P>
+__global__ void __launch_bounds__(NT / P) k_logits_part(const float* __restrict__ logits, int64_t V,
+                                                         const uint8_t* __restrict__ mask,
+                                                         RowStats* __restrict__ part) {
+  __shared__ RowStats sh[NT / P / 64 + 1];
+  const int64_t t = blockIdx.x / P;
+  if (!mask[t]) return;
+  const int vt = (int)(blockIdx.x % P) * (NT / P) + threadIdx.x;
+  const float* z = logits + t * V;
+  RowStats r = {-INFINITY, 0.f, 0.f};
+  const RowView rv(z, V);
+  const float4* z4 = (const float4*)rv.z4;
+  constexpr int UN = 16;
+  int64_t j = vt;
+  for (; j + (UN - 1) * NT < rv.n4; j += UN * NT) {
+    float4 q[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) q[u] = z4[j + u * NT];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) acc4(r, q[u]);
+  }
+  float4 q[UN];
+#pragma unroll
+  for (int u = 0; u < UN; ++u)
+    if (j + u * NT < rv.n4) q[u] = z4[j + u * NT];
+#pragma unroll
+  for (int u = 0; u < UN; ++u)
+    if (j + u * NT < rv.n4) acc4(r, q[u]);
+  if (rv.has_extra(vt)) acc1(r, z[rv.extra(vt)]);
+  r = block_stats<NT / P>(r, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
 // ---- fused: statistics, loss terms and d_logits (rft_ppo_clip_fused_logits),
@@ -241,7 +295,7 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
   float* out = dl + t * V;
   int k = kidx[t];
   if (k < 0) {
-    zero_row(out, V);
+    zero_row(out, V, threadIdx.x);
     if (threadIdx.x == 0) {
       logp[t] = 0.f;
       if (ent) ent[t] = 0.f;
@@ -282,7 +336,7 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
   __syncthreads();
   float c = row_c, L = sh[NT / 64].m;
   int y = ids[t];
-  row_pass2<true>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out);
+  row_pass2<true>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out, threadIdx.x);
 }
 
 // ---- fused, with the row kept on chip: the first REG*NTC float4 of the row
@@ -339,7 +393,7 @@ __global__ void __launch_bounds__(NTC, WPS) k_logits_fused_cached(
       for (int64_t j = tid, o = vo; j < n4; j += NTC, o += SU)
         __builtin_amdgcn_raw_buffer_store_b128((v4i)zz, rout, (uint32_t)o, 0, 2);
     } else {
-      zero_row(out, V);
+      zero_row(out, V, threadIdx.x);
     }
     if (tid == 0) {
       logp[t] = 0.f;
@@ -463,13 +517,29 @@ hipError_t launch_logits_stats(const float* logits, const rft_tokens& tok, int64
   return hipGetLastError();
 }
 
+// log2 of the parts a row is cut into: as many as the CUs hold beside the other
+// rows (at most the eight waves of a row), if a part saves at least 32768 logits'
+// time (8 us) for the launch that it costs; 0 = one workgroup per row.
+static hipError_t row_parts(int64_t T, int64_t V, int* lp) {
+  int ncu = 0;
+  hipError_t e = cu_count(&ncu);
+  if (e != hipSuccess) return e;
+  *lp = 0;
+  for (int k = 1; k <= 3; ++k)
+    if ((T << k) <= ncu && V - (V >> k) >= 32768) *lp = k;
+  return hipSuccess;
+}
+
 hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t V,
                              const float* lse, const float* grad, const float* egrad,
                              const float* ent, float* dl, hipStream_t s) {
   if (tok.T <= 0) return hipSuccess;
+  int lp = 0;
+  hipError_t e = row_parts(tok.T, V, &lp);
+  if (e != hipSuccess) return e;
   auto k = egrad ? lg::k_logits_bwd<true> : lg::k_logits_bwd<false>;
-  k<<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask, tok.token_ids, lse, grad, egrad,
-                                       ent, dl);
+  k<<<(unsigned)(tok.T << lp), lg::NT >> lp, 0, s>>>(logits, V, tok.mask, tok.token_ids, lse, grad,
+                                                     egrad, ent, dl, lp);
   return hipGetLastError();
 }
 
@@ -507,6 +577,29 @@ hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const
                                float* grad, float* dl, LossPartial* parts, LossPartial* parts2,
                                rft_ppo_stats* st, hipStream_t s) {
   hipError_t e = hipSuccess;
+  int lp = 0;
+  if (tok.T > 0 && (e = row_parts(tok.T, V, &lp)) != hipSuccess) return e;
+  // the parts (12 bytes each) take the room of the T row partials and of the
+  // one after them (workspaces are whole multiples of 256 bytes)
+  while (lp > 0 && (tok.T << lp) * (int64_t)sizeof(RowStats) > (char*)parts2 - (char*)parts + 256) --lp;
+  // few rows: launch_few_terms does the bookkeeping
+  const bool few = lp > 0 && tok.n_seq <= kFewSeq;
+  if (!few && (e = launch_tokmeta(tok, m, s)) != hipSuccess) return e;
+  if (few) {
+    RowStats* const part = (RowStats*)parts;
+    const unsigned nb = (unsigned)(tok.T << lp);
+    if (lp == 3) lg::k_logits_part<8><<<nb, lg::NT / 8, 0, s>>>(logits, V, tok.mask, part);
+    else if (lp == 2) lg::k_logits_part<4><<<nb, lg::NT / 4, 0, s>>>(logits, V, tok.mask, part);
+    else lg::k_logits_part<2><<<nb, lg::NT / 2, 0, s>>>(logits, V, tok.mask, part);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_few_terms(logits, tok, m, V, 1 << lp, old, ref, adv, c, logp, ent, lse, grad,
+                              parts, st, s)) != hipSuccess)
+      return e;
+    const float* const terms = (const float*)parts;
+    const bool bonus = c.ent_coef > 0.f;
+    return launch_logits_bwd(logits, tok, V, terms, terms + tok.T, bonus ? terms + 2 * tok.T : nullptr,
+                             bonus ? terms + 3 * tok.T : nullptr, dl, s);
+  }
   if (tok.T > 0) {
     // buffer descriptors span one row: 32-bit byte offsets
     if (V > ((int64_t)1 << 28)) {

@@ -32,12 +32,12 @@ __global__ void __launch_bounds__(kMergeThreads) k_step_rows(
     const float* __restrict__ ref, const float* __restrict__ adv, LossConst c,
     float* __restrict__ logp, float* __restrict__ ent, float* __restrict__ lse,
     float* __restrict__ grad, float* __restrict__ ce, float* __restrict__ cmu) {
-  __shared__ LseSum sh[kMergeThreads];
+  __shared__ RowStats sh[kMergeThreads];
   const int64_t kl = (int64_t)blockIdx.x * kMergeRows + threadIdx.x % kMergeRows;  // row within the chunk
   const int64_t k = c0 + kl;                                                       // compacted row
   const bool on = kl < Tc && k < (int64_t)meta[0];
   const int64_t ko = on ? kl : 0;
-  const LseSum r = merge_tiles(pm + ko, ps + ko, pu + ko, Tc, ntiles, on, sh);
+  const RowStats r = merge_tiles(pm + ko, ps + ko, pu + ko, Tc, ntiles, on, sh);
   if (threadIdx.x >= kMergeRows || !on) return;
   const int t = rows[k];
   const float m = r.m, sm = r.s, u = r.u;

@@ -751,7 +751,6 @@ rft_status rft_ppo_clip_fused_logits(const rft_tokens* tok, const float* logits,
   if ((st = check_ws(fn, ws, ws_bytes, w.bytes))) return st;
   w = carve_loss(ws, *tok, true);
   hipStream_t s = (hipStream_t)stream;
-  RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   LossConst c = loss_const(params, V, *tok);
   RFT_HIP(launch_logits_fused(logits, *tok, w.m, V, old_logp,
                               ref_logp, adv, c, logp, entropy,

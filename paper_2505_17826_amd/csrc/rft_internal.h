@@ -122,6 +122,20 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float& u, float m2
   m = M;
 }
 
+// Online log-sum-exp state (max, sum exp, sum exp * z), and the merge of N (a
+// power of two) of them as a binary tree, into v[0].
+struct RowStats {
+  float m, s, u;
+};
+template <int N>
+__device__ __forceinline__ void tree_merge(RowStats (&v)[N]) {
+#pragma unroll
+  for (int w = 1; w < N; w <<= 1)
+#pragma unroll
+    for (int i = 0; i < N; i += 2 * w)
+      lse_merge(v[i].m, v[i].s, v[i].u, v[i + w].m, v[i + w].s, v[i + w].u);
+}
+
 // The partials of one row over all vocabulary tiles (pm, ps, pu point at the
 // row's entry of tile 0, tiles `ld` apart), merged by the threads of a
 // 512-thread block: kMergeRows rows per block, kMergeSegs threads per row,
@@ -134,23 +148,20 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float& u, float m2
 // and 27 us at 9200.  Call it from
 // every thread of the block; `on` is false for rows that do not exist.
 constexpr int kMergeRows = 32, kMergeSegs = 16, kMergeThreads = kMergeRows * kMergeSegs;
-struct LseSum {
-  float m, s, u;
-};
-__device__ __forceinline__ void lse_add(LseSum& r, float M, float a, float b, float c) {
+__device__ __forceinline__ void lse_add(RowStats& r, float M, float a, float b, float c) {
   // an empty partial (b == 0) adds nothing whatever its maximum
   const float e = b == 0.f ? 0.f : exp2f((a - M) * kLog2e);
   r.s = fmaf(b, e, r.s);
   r.u = fmaf(c, e, r.u);
 }
-__device__ __forceinline__ LseSum merge_tiles(const float* __restrict__ pm,
+__device__ __forceinline__ RowStats merge_tiles(const float* __restrict__ pm,
                                               const float* __restrict__ ps,
                                               const float* __restrict__ pu, int64_t ld, int ntiles,
-                                              bool on, LseSum* sh) {
+                                              bool on, RowStats* sh) {
   const int g = threadIdx.x / kMergeRows;
   const int per = (ntiles + kMergeSegs - 1) / kMergeSegs;
   const int j1 = min(ntiles, (g + 1) * per);
-  LseSum r = {-INFINITY, 0.f, 0.f};
+  RowStats r = {-INFINITY, 0.f, 0.f};
   if (on) {
     for (int j = g * per; j < j1; j += 8) {
       float a[8], b[8], c[8];
@@ -164,7 +175,7 @@ __device__ __forceinline__ LseSum merge_tiles(const float* __restrict__ pm,
       float M = r.m;
 #pragma unroll
       for (int q = 0; q < 8; ++q) M = fmaxf(M, b[q] == 0.f ? -INFINITY : a[q]);
-      const LseSum p = r;
+      const RowStats p = r;
       r = {M, 0.f, 0.f};
       lse_add(r, M, p.m, p.s, p.u);
 #pragma unroll
@@ -176,7 +187,7 @@ __device__ __forceinline__ LseSum merge_tiles(const float* __restrict__ pm,
   if (g == 0 && on) {
 #pragma unroll 4
     for (int k = 1; k < kMergeSegs; ++k) {
-      const LseSum q = sh[k * kMergeRows + threadIdx.x];
+      const RowStats q = sh[k * kMergeRows + threadIdx.x];
       lse_merge(r.m, r.s, r.u, q.m, q.s, q.u);
     }
   }
@@ -425,6 +436,13 @@ hipError_t launch_logits_stats(const float* logits, const rft_tokens& tok, int64
 hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t V,
                              const float* lse, const float* grad, const float* egrad,
                              const float* ent, float* dl, hipStream_t s);
+constexpr int64_t kFewSeq = 2048;  // rollouts of the bookkeeping in one workgroup
+// Row terms of a handful of rows from their parts' statistics (k_logits_part):
+// parts [T][P] in scratch, which then gets lse, c, e and entropy [T] each.
+hipError_t launch_few_terms(const float* logits, const rft_tokens& tok, const TokMeta& m, int64_t V,
+                            int P, const float* old, const float* ref, const float* adv,
+                            const LossConst& c, float* logp, float* ent, float* lse, float* grad,
+                            void* scratch, rft_ppo_stats* st, hipStream_t s);
 hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const TokMeta& m,
                                int64_t V, const float* old, const float* ref, const float* adv,
                                const LossConst& c, float* logp, float* ent, float* lse,

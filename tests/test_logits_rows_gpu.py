@@ -1,5 +1,6 @@
 """The loss-only kernels over the lengths and alignments of a row: the edges of
-the on-chip variants (chunks of 2048 logits: 6, 17, 31 and 73-75 of them), rows
+the on-chip variants (chunks of 2048 logits: 6, 17, 31 and 73-75 of them), a
+handful of rows cut into parts, rows
 whose start and length are no multiple of 16 bytes, d_logits aligned unlike the
 logits, very short rows; the fused, statistics-only and d_logits-only calls give
 the same bits, and float64's values.
@@ -23,13 +24,16 @@ def _at(x, shift):
 
 
 @pytest.mark.parametrize("ent", [0.0, 0.02])
-@pytest.mark.parametrize("V,shift,dshift", [
-    (1, 0, 0), (2, 3, 1), (3, 1, 0), (5, 2, 2), (2047, 0, 0), (6 * 2048, 0, 1),
-    (6 * 2048 + 1, 1, 1), (17 * 2048 + 3, 0, 0), (17 * 2048 + 4, 2, 0), (31 * 2048, 0, 0),
-    (31 * 2048 + 7, 3, 3), (75 * 2048 - 2, 0, 0), (73 * 2048 + 9, 1, 2)])
-def test_row_lengths_and_alignments(V, shift, dshift, ent):
-    T, n_seq = 24, 3
-    print(f"[row] V={V} shift={shift} dshift={dshift} ent={ent}", flush=True)
+@pytest.mark.parametrize("T,V,shift,dshift", [
+    (24, 1, 0, 0), (24, 2, 3, 1), (24, 3, 1, 0), (24, 5, 2, 2), (24, 2047, 0, 0),
+    (24, 6 * 2048, 0, 1), (24, 6 * 2048 + 1, 1, 1), (24, 17 * 2048 + 3, 0, 0),
+    (200, 17 * 2048 + 4, 2, 0), (200, 31 * 2048, 0, 0), (160, 31 * 2048 + 7, 3, 3),
+    (160, 75 * 2048 - 2, 0, 0), (160, 73 * 2048 + 9, 1, 2),
+    # rows cut into 8, 4 and 2 parts
+    (12, 37449, 0, 0), (12, 37450, 1, 0), (32, 75 * 2048 - 2, 0, 0), (33, 73 * 2048 + 9, 1, 2),
+    (64, 31 * 2048 + 7, 3, 3), (65, 65536, 0, 1), (128, 65537, 2, 2), (129, 65536, 0, 0)])
+def test_row_lengths_and_alignments(T, V, shift, dshift, ent):
+    print(f"[row] T={T} V={V} shift={shift} dshift={dshift} ent={ent}", flush=True)
     g = torch.Generator().manual_seed(V + shift)
     z0 = torch.randn((T, V), generator=g) * 2
     if V > 4:
@@ -42,7 +46,7 @@ def test_row_lengths_and_alignments(V, shift, dshift, ent):
     z0[0] = float("nan")  # masked rows are never read
     m = mask.bool()
     z = _at(z0, shift)
-    start = torch.tensor([0, 8, 16, 24], dtype=torch.int32, device=DEV)
+    start = torch.tensor([0, 8, T // 2 + 3, T], dtype=torch.int32, device=DEV)
     tok = R.Tokens(start, mask.to(DEV), ids.to(DEV))
     t = lambda x: x.to(DEV)  # noqa: E731
     zm = z0[m].double()
