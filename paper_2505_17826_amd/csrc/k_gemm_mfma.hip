@@ -39,6 +39,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
+#include <type_traits>
 
 #include "rft_internal.h"
 
@@ -783,11 +784,8 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   }
   const int nkt = (K + BK - 1) / BK, ks0 = EPI == EPI_STORE ? sl * ((nkt + S - 1) / S) : 0;
   const int nk = EPI == EPI_STORE && S > 1 ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
-  constexpr int NLOAD = kNLoad4<EPI>;
-  constexpr int RA = BM4 / NLOAD, RB = BN / NLOAD;  // rows of A and of B per loader wave
+  constexpr int RA = BM4 / 8, RB = BN / 8;  // rows of A and of B per wave
   static_assert(RA % 16 == 0 && RB % 16 == 0, "offset parity follows the row-pair swizzle");
-  const bool loader = wid < NLOAD;
-  const int lw = wid % NLOAD;
   const int m0 = mt * BM4, n0 = nt * BN;
   const int P0 = m0 >> 8, base0 = m0 & 255;
   const int64_t pa = (int64_t)256 * g.lda;  // elements per panel of A
@@ -805,20 +803,23 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
 #pragma unroll
   for (int q = 0; q < 2; ++q)
     vq[q] = (uint32_t)((lane >> 3) * 128 + (((lane & 7) ^ (lane >> 4) ^ (q * 4)) << 4));
-  auto load = [&](char* dst, int k0) {
+  auto load_a = [&](char* dst, int k0) {
     const uint32_t kofs = (uint32_t)k0 * 512u;  // a 64-column block is 32 KiB
 #pragma unroll
-    for (int p = 0; p < RA / 8; ++p) {  // A: rows lw * RA + 8 p ..
-      const int R0 = lw * RA + 8 * p;
+    for (int p = 0; p < RA / 8; ++p) {  // rows wid * RA + 8 p ..
+      const int R0 = wid * RA + 8 * p;
       const int pr = base0 + R0;  // row from the start of P0 (>= 256: in P1)
       const uint32_t so = __builtin_amdgcn_readfirstlane(
           kofs + (uint32_t)((pr & 255) * 128) + (uint32_t)(pr >> 8) * pbytes);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr)(dst + R0 * 128), 16, vq[p & 1], so,
                                                0, 0);
     }
+  };
+  auto load_b = [&](char* dst, int k0) {
+    const uint32_t kofs = (uint32_t)k0 * 512u;
 #pragma unroll
-    for (int p = 0; p < RB / 8; ++p) {  // B: rows lw * RB + 8 p ..
-      const int R0 = lw * RB + 8 * p;
+    for (int p = 0; p < RB / 8; ++p) {  // rows wid * RB + 8 p ..
+      const int R0 = wid * RB + 8 * p;
       const uint32_t so = __builtin_amdgcn_readfirstlane(kofs + (uint32_t)(R0 * 128));
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, (lds_ptr)(dst + A_BYTES4 + R0 * 128), 16,
                                                vq[p & 1], so, 0, 0);
@@ -830,38 +831,67 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   for (int i = 0; i < 6; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc4[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-  if (nk > 0 && loader) load(lds, ks0 * BK);
-  __syncthreads();  // first stage visible to every wave
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk && loader) load(lds + ((kt + 1) & 1) * STAGE4, (ks0 + kt + 1) * BK);
-    const char* As = lds + (kt & 1) * STAGE4;
-    const char* Al = As + (wm * 96 + r16) * 128;
-    const char* Bl = As + A_BYTES4 + (wn * 128 + r16) * 128;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int cho = ((ks * 4 + q4) ^ ((r16 >> 1) & 7)) << 4;
-      bf16x8 a[6];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) a[i] = *(const bf16x8*)(Al + i * 2048 + cho);
-#pragma unroll
-      for (int jh = 0; jh < 4; ++jh) {
-        bf16x8 b[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8*)(Bl + (jh * 2 + j) * 2048 + cho);
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc4[i][jh * 2 + j] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][jh * 2 + j], 0, 0, 0);
-      }
-    }
-    // this wave's loads of the next stage have landed and its reads of this
-    // stage are complete before the barrier
-    wait_vm();
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    barrier_lds();
+  if (nk > 0) {
+    load_a(lds, ks0 * BK);
+    load_b(lds, ks0 * BK);
   }
+  wait_vm();
+  __syncthreads();  // first stage visible to every wave
+  const bool late = wid >= 4;
+  if (late) barrier_lds();
+  bf16x8 a[6], b[4];
+  const char *Al, *Bl;
+  auto read_a = [&](int ks) {
+    const int cho = ((ks * 4 + q4) ^ ((r16 >> 1) & 7)) << 4;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) a[i] = *(const bf16x8*)(Al + i * 2048 + cho);
+  };
+  auto read_b = [&](int ks, int h) {
+    const int cho = ((ks * 4 + q4) ^ ((r16 >> 1) & 7)) << 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = *(const bf16x8*)(Bl + (h * 4 + j) * 2048 + cho);
+  };
+  auto multiply = [&](auto hc) {
+    constexpr int h = decltype(hc)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this phase's fragments
+    barrier_lds();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc4[i][h * 4 + j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][h * 4 + j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    barrier_lds();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr std::integral_constant<int, 0> h0{};
+  constexpr std::integral_constant<int, 1> h1{};
+  for (int kt = 0; kt < nk; ++kt) {
+    const char* As = lds + (kt & 1) * STAGE4;
+    char* const nxt = lds + ((kt + 1) & 1) * STAGE4;
+    const bool more = kt + 1 < nk;
+    Al = As + (wm * 96 + r16) * 128;
+    Bl = As + A_BYTES4 + (wn * 128 + r16) * 128;
+    read_a(0);
+    read_b(0, 0);
+    if (more) load_a(nxt, (ks0 + kt + 1) * BK);
+    multiply(h0);
+    read_b(0, 1);
+    if (more) load_b(nxt, (ks0 + kt + 1) * BK);
+    multiply(h1);
+    read_a(1);
+    read_b(1, 0);
+    multiply(h0);
+    read_b(1, 1);
+    wait_vm();
+    multiply(h1);
+  }
+  if (!late) barrier_lds();
   // element q of tile (i, j) is row wm*96 + i*16 + q4*4 + q and column
   // wn*128 + j*16 + r16 of the workgroup tile
   if constexpr (EPI == EPI_STORE) {
