@@ -105,55 +105,84 @@ struct Args {
   float* C; int64_t ldc; int accumulate; int c_scatter;  // EPI_STORE
   int sel;            // EPI_STORE with both tile sizes launched: 1 = the 384-row kernel runs
   int ncu;            //   only if prefer384(M, N, slices, ncu), 2 = the 256-row kernel only if not
-  // EPI_STORE over slices of K (pick_slices): slice s of an M x N result goes
-  // to part + s M N (row m at m N), summed by k_sum_slices; 0 = never
+  // EPI_STORE over slices of K (pick_plan): slice s of the rows from Mf on goes to
+  // part + s (M - Mf) N (row m at (m - Mf) N), summed by k_sum_slices; 0 = never
   float* part; int64_t part_elems;
 };
 
 // fp32-store GEMM on tile-blocked operands: whether the 384 x 256 tile beats
 // the 256 x 256 one for an M x N result on ncu compute units.  Tiles run in
 // rounds of ncu (one workgroup per CU), so the time is about ceil(tiles / ncu)
-// tile times; a 384-row tile takes 1.43 times a 256-row one (1.5 times the
-// work at ~5% more flops per cycle, measured on the 7B shapes).  E.g. d_hidden
-// of 131072 rows and d = 3584: 19 rounds of 384 (27.2) against 28 of 256;
-// with d = 1536: 9 (12.9) against 12; 36901 rows, d = 3584: 6 (8.6) against 8.
+// tile times; a 384-row tile takes 1.37 times a 256-row one (measured per round:
+// d_weight 1.36 at d = 3584 and 1.33 at 1536, d_hidden 1.38).  E.g. d_weight of
+// d = 1536, V = 151936: 10 rounds of 384 (13.7; 14.15 ms) against 14 of 256 (14.85
+// ms); d_hidden of 42000 rows, d = 3584: 7 (9.6; 36.3 ms) against 10 (37.5 ms).
 // Slices of K multiply the tiles of both.
 __host__ __device__ inline bool prefer384(int64_t M, int64_t N, int64_t slices, int64_t ncu) {
   const int64_t tn = (N + 255) / 256 * slices;
   const int64_t r4 = ((M + 383) / 384 * tn + ncu - 1) / ncu;
   const int64_t r2 = ((M + 255) / 256 * tn + ncu - 1) / ncu;
-  return r4 * 143 < r2 * 100;
+  return r4 * 137 < r2 * 100;
 }
 
-// Slices of K for an M x N result with K long and few tiles (d_hidden of a
-// micro-batch: 5 x 14 tiles of 256 x 256 at 1152 rows, d = 3584, each K =
-// 152064 long, ran on 70 of 256 CUs: 3.5 ms whatever the rows).  Lane l of the
-// wave prices l + 1 slices and the cheapest wins: rounds of tiles over the
-// CUs, each a slice of K long (26 ns per K for a 256 x 256 tile per CU, 3 us
-// for its start and its stores), plus the pass over the partial sums (8 bytes
-// per element and slice at 5 TB/s, 5 us for its launch).  At most kMaxSlices
-// slices, kSliceRounds rounds (the grid's size) and the scratch; one slice from
-// kSliceRounds / 2 rounds on, where the last round weighs little.  Every wave
-// of the GEMM and of the sum computes the same number from the same count.
-// Independent of the tile, so both tiles give the same bits.  Measured at d =
-// 3584, V = 152064: 1152 rows 3.52 -> 1.19 ms, 2560 rows 3.57 -> 2.30 ms, and
-// 26 / 69 us for the sum.
-constexpr int kMaxSlices = 16, kSliceRounds = 6;
-__device__ __forceinline__ int pick_slices(int M, int N, int K, int ncu, int64_t part_elems) {
-  const int64_t t64 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (t64 == 0 || 2 * t64 >= (int64_t)kSliceRounds * ncu) return 1;
-  // integers (M N < 2^26 here): the same in every kernel whatever the compiler
-  // contracts
-  const int tiles = (int)t64, S = 1 + (int)(threadIdx.x & 63);
-  int cost = (tiles * S + ncu - 1) / ncu * (26 * K / S + 3000);
-  if (S > 1) cost += 5000 + M * N / 625 * S;
-  const bool ok = S == 1 || (S <= kMaxSlices && tiles * S <= kSliceRounds * ncu &&
-                             (int64_t)S * M * N <= part_elems && S * BK <= K);
-  if (!ok) cost = 0x7fffffff;
-  int best = cost;
+// How an M x N result with K long is cut (d_hidden; K = the vocabulary): rows
+// [0, Mf) in whole-K tiles, rows [Mf, M) in S slices of K whose partial sums go
+// to scratch.
+//  - Few tiles (below kSliceRounds / 2 rounds): Mf = 0.  5 x 14 tiles of 256 x 256
+//    at 1152 rows, d = 3584, each K = 152064 long, ran on 70 of 256 CUs: 3.5 ms
+//    whatever the rows.  Lane l of the wave prices l + 1 slices and the cheapest
+//    wins: rounds of tiles over the CUs, each a slice of K long (26 ns per K for a
+//    256 x 256 tile per CU, 3 us for its start and its stores), plus the pass over
+//    the partial sums (8 bytes per element and slice at 5 TB/s, 5 us for its
+//    launch), at most kSliceRounds rounds.  Measured at d = 3584, V = 152064: 1152
+//    rows 3.52 -> 1.19 ms, 2560 rows 3.57 -> 2.30 ms, and 26 / 69 us for the sum.
+//  - Many tiles: whole rounds of 384-row tiles (in steps of 768 rows, which both
+//    tiles divide), and the rows of the last, partial round in S slices, so that
+//    every CU ends within 1 / S of a tile.  At 42000 rows 7 rounds with 4 tiles in
+//    the last took 36.3 ms, 6.02 rounds' worth takes 32.2.
+// At most kMaxSlices slices and the scratch.  Every wave of the GEMM and of the
+// sum computes the same plan (in integers: whatever the compiler contracts) from
+// the same count, and it does not depend on the tile, so both give the same bits.
+constexpr int kMaxSlices = 16, kSliceRounds = 6, kTailRounds = 4;
+struct Plan {
+  int Mf, S;
+};
+__device__ __forceinline__ Plan pick_plan(int M, int N, int K, int ncu, int64_t part_elems) {
+  const int tn = (N + 255) / 256, S = 1 + (int)(threadIdx.x & 63);
+  const int64_t t64 = (int64_t)((M + 255) / 256) * tn;
+  if (t64 == 0) return {0, 1};
+  int Mf = 0;
+  bool ok = S <= kMaxSlices && S * BK <= K;
+  int64_t cost;
+  if (2 * t64 < (int64_t)kSliceRounds * ncu) {
+    const int tiles = (int)t64;
+    ok = ok && tiles * S <= kSliceRounds * ncu;
+    cost = (int64_t)((tiles * S + ncu - 1) / ncu) * (26 * (int64_t)K / S + 3000);
+    if (S > 1) cost += 5000 + (int64_t)M * N / 625 * S;
+  } else {
+    const int64_t n4 = (int64_t)((M + 383) / 384) * tn;  // tiles of 384 rows
+    Mf = (int)(n4 / ncu * ncu / (2 * tn)) * 768;
+    const int rest = (int)(n4 - (int64_t)(Mf / 384) * tn), rem = (int)(n4 % ncu);
+    const int64_t tile = 26 * (int64_t)K * 137 / 100;  // ns
+    ok = ok && Mf < M && rest * S <= kTailRounds * ncu;
+    cost = S > 1 ? rem * tile / ncu + tile / S + 5000 + (int64_t)rest * 157 * S
+                 : (rem > 0 ? tile : 0);
+  }
+  if (S > 1 && !(ok && (int64_t)S * (M - Mf) * N <= part_elems)) cost = INT64_MAX;
+  int64_t best = cost;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, 64));
-  return 1 + (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(cost == best));
+  for (int o = 32; o > 0; o >>= 1) {
+    const int64_t other = __shfl_xor((long long)best, o, 64);
+    best = other < best ? other : best;
+  }
+  const int pick = 1 + (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(cost == best));
+  return {__builtin_amdgcn_readfirstlane(pick > 1 ? Mf : M), __builtin_amdgcn_readfirstlane(pick)};
+}
+
+// Whether the 384-row kernel takes the result: with a sliced tail its cheaper
+// rows decide (the last round is then no matter of whole tiles).
+__device__ __forceinline__ bool use384(const Plan& pl, int M, int N, int ncu) {
+  return pl.S > 1 && pl.Mf > 0 ? true : prefer384(M, N, pl.S, ncu);
 }
 
 // Item b of an S-sliced M x N result: XCD b % 8 takes a contiguous run of
@@ -162,6 +191,7 @@ __device__ __forceinline__ int pick_slices(int M, int N, int K, int ncu, int64_t
 // six panels of each operand through its L2.
 constexpr int kBand = 6;
 __device__ __forceinline__ bool slice_of(int b, int nTm, int nTn, int S, int& sl, int& mt, int& nt) {
+  // nTm: M-tiles of the sliced rows
   const int items = nTm * nTn * S, per = (items + 7) / 8;
   const int i = (b & 7) * per + (b >> 3);
   if ((b >> 3) >= per || i >= items) return false;
@@ -265,7 +295,7 @@ __device__ __forceinline__ bool tile_of(int b, int nTm, int nTn, int& mt, int& n
 // Workgroups needed for nTm x nTn tiles in that order (non-decreasing in
 // nTm, so a grid sized for the largest M covers every smaller M).
 template <int SG>
-inline int64_t grid_tiles(int64_t nTm, int64_t nTn) {
+__host__ __device__ inline int64_t grid_tiles(int64_t nTm, int64_t nTn) {
   const int64_t full = nTm / (8 * SG);
   const int64_t R = nTm - full * 8 * SG;
   return 8 * (full * SG * nTn + (R * nTn + 7) / 8);
@@ -349,20 +379,31 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
   const int N = g.N;
   const int NB = g.NB > 0 ? g.NB : N;
   if (EPI == EPI_STORE && g.k_from_cnt && K == 0 && g.accumulate) return;  // nothing to add
-  int S = 1, sl = 0;
-  if (EPI == EPI_STORE && g.part) S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, K, g.ncu, g.part_elems));
-  if (EPI == EPI_STORE && g.sel == 2 && prefer384(M, N, S, g.ncu)) return;  // the 384-row kernel's
-  const int nTm = (M + BM - 1) / BM, nTn = (N + BN - 1) / BN;
+  Plan pl = {M, 1};
+  if (EPI == EPI_STORE && g.part) pl = pick_plan(M, N, K, g.ncu, g.part_elems);
+  const int S = pl.S;
+  int sl = 0;
+  if (EPI == EPI_STORE && g.sel == 2 && use384(pl, M, N, g.ncu)) return;  // the 384-row kernel's
   // The grid is sized for the largest possible M; workgroups without a tile
   // for the device count exit at once.
+  const int nTn = (N + BN - 1) / BN;
   int mt, nt;
+  bool sliced = false;
   if (EPI == EPI_STORE && S > 1) {
-    if (!slice_of((int)blockIdx.x, nTm, nTn, S, sl, mt, nt)) return;
-  } else if (!tile_of<kSG<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) {
+    // the whole-K tiles of rows [0, Mf), then the slices of the rest
+    const int nTf = pl.Mf / BM, first = (int)grid_tiles<kSG<EPI>>(nTf, nTn);
+    sliced = (int)blockIdx.x >= first;
+    if (sliced) {
+      if (!slice_of((int)blockIdx.x - first, (M - pl.Mf + BM - 1) / BM, nTn, S, sl, mt, nt)) return;
+      mt += nTf;
+    } else if (!tile_of<kSG<EPI>>((int)blockIdx.x, nTf, nTn, mt, nt)) {
+      return;
+    }
+  } else if (!tile_of<kSG<EPI>>((int)blockIdx.x, (M + BM - 1) / BM, nTn, mt, nt)) {
     return;
   }
   const int nkt = (K + BK - 1) / BK, ks0 = EPI == EPI_STORE ? sl * ((nkt + S - 1) / S) : 0;
-  const int nk = EPI == EPI_STORE && S > 1 ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
+  const int nk = EPI == EPI_STORE && sliced ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
 
   // per-lane load geometry (see load_stage): row w*64 + p*8 + (lane>>3)
   constexpr int NLOAD = kNLoad<EPI>;
@@ -708,8 +749,9 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
           const int rl = wm * 64 + i * 16 + q4 * 4 + q;
           const int m = m0 + rl;
           if (m >= M) continue;
-          float* const dst = S > 1 ? g.part + ((int64_t)sl * M + m) * N : g.C + (int64_t)rp_i[rl] * g.ldc;
-          const bool add = g.accumulate && S == 1;
+          float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
+                                    : g.C + (int64_t)rp_i[rl] * g.ldc;
+          const bool add = g.accumulate && !sliced;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int col = n0 + wn * 128 + j * 16 + r16;
@@ -730,8 +772,7 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
 // fp32 store of the step's dH and dW (EPI_STORE), the fused step's forward
 // (EPI_STATS_Y) and the forward of rft_token_logprobs given the workspace for
 // blocked operands (EPI_STATS).  Eight waves of 96 x 128 (6 x 8 tiles of 16x16x32, 192
-// accumulator registers), two 80 KiB stages (all of the LDS), two loader
-// waves.  17% fewer operand bytes and 22% fewer LDS fragment bytes per flop
+// accumulator registers), two 80 KiB stages (all of the LDS).  17% fewer operand bytes and 22% fewer LDS fragment bytes per flop
 // than the 256 x 256 tile; the per-element k order is the same, so the results
 // are bit-identical to k_gemm's.  A 384-row tile starts at row 0 or 128 of a
 // 256-row panel P0 of A and continues into P1 = P0 + 1; one descriptor covers
@@ -743,11 +784,22 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
 // per-instruction offsets held in registers across the loop spilled).  The LDS
 // layout, swizzle and fragment reads are those of k_gemm; rows 16 i + r16 of a
 // wave's fragments share the swizzle (r16 >> 1) & 7.
+// Schedule: waves 0-3 and 4-7 (one of each on every SIMD) run half a phase apart,
+// which one barrier more before the loop of waves 4-7 and one more after that of
+// waves 0-3 make: between two barriers one group reads the fragments of its next
+// 24 matrix instructions and issues loads, the other runs its 24 at raised
+// priority.  A step has four such phases per wave; its share of the next stage's
+// loads goes out in the first two, once every wave has passed the barrier after
+// its last reads of that buffer, and is waited for in the last one, before the
+// barrier that precedes the first read.  The matrix pipe is busy 81% of the
+// cycles in d_weight (42000 rows, d = 3584, V = 152064), 72% with two loader waves
+// and one barrier per step; the card's power limit lowers the clock from 1.75 to
+// 1.65 GHz, so 35.3 -> 33.4 ms remain (1.38 PFLOP/s), and 1% of the forward.  The
+// same schedule with two phases of 32 made the 256 x 256 tile 5% slower.
 constexpr int BM4 = 384;
 constexpr int A_BYTES4 = BM4 * BK * 2;      // 48 KiB
 constexpr int STAGE4 = A_BYTES4 + B_BYTES;  // 80 KiB
 template <int EPI> constexpr int kSG4 = EPI == EPI_STORE ? 4 : 8;
-template <int EPI> constexpr int kNLoad4 = 2;
 // forward epilogue's LDS after the main loop: the y staging tile, the two
 // column halves' row maxima [2][384], the wn = 1 half's partials [384][3] and
 // the rows' token ids [384]
@@ -772,18 +824,29 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   }
   const int N = g.N;
   if (EPI == EPI_STORE && g.k_from_cnt && K == 0 && g.accumulate) return;  // nothing to add
-  int S = 1, sl = 0;
-  if (EPI == EPI_STORE && g.part) S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, K, g.ncu, g.part_elems));
-  if (EPI == EPI_STORE && g.sel == 1 && !prefer384(M, N, S, g.ncu)) return;  // the 256-row kernel's
-  const int nTm = (M + BM4 - 1) / BM4, nTn = (N + BN - 1) / BN;
+  Plan pl = {M, 1};
+  if (EPI == EPI_STORE && g.part) pl = pick_plan(M, N, K, g.ncu, g.part_elems);
+  const int S = pl.S;
+  int sl = 0;
+  if (EPI == EPI_STORE && g.sel == 1 && !use384(pl, M, N, g.ncu)) return;  // the 256-row kernel's
+  const int nTn = (N + BN - 1) / BN;
   int mt, nt;
+  bool sliced = false;
   if (EPI == EPI_STORE && S > 1) {
-    if (!slice_of((int)blockIdx.x, nTm, nTn, S, sl, mt, nt)) return;
-  } else if (!tile_of<kSG4<EPI>>((int)blockIdx.x, nTm, nTn, mt, nt)) {
+    // the whole-K tiles of rows [0, Mf), then the slices of the rest
+    const int nTf = pl.Mf / BM4, first = (int)grid_tiles<kSG4<EPI>>(nTf, nTn);
+    sliced = (int)blockIdx.x >= first;
+    if (sliced) {
+      if (!slice_of((int)blockIdx.x - first, (M - pl.Mf + BM4 - 1) / BM4, nTn, S, sl, mt, nt)) return;
+      mt += nTf;
+    } else if (!tile_of<kSG4<EPI>>((int)blockIdx.x, nTf, nTn, mt, nt)) {
+      return;
+    }
+  } else if (!tile_of<kSG4<EPI>>((int)blockIdx.x, (M + BM4 - 1) / BM4, nTn, mt, nt)) {
     return;
   }
   const int nkt = (K + BK - 1) / BK, ks0 = EPI == EPI_STORE ? sl * ((nkt + S - 1) / S) : 0;
-  const int nk = EPI == EPI_STORE && S > 1 ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
+  const int nk = EPI == EPI_STORE && sliced ? min(nkt - ks0, (nkt + S - 1) / S) : nkt;
   constexpr int RA = BM4 / 8, RB = BN / 8;  // rows of A and of B per wave
   static_assert(RA % 16 == 0 && RB % 16 == 0, "offset parity follows the row-pair swizzle");
   const int m0 = mt * BM4, n0 = nt * BN;
@@ -902,9 +965,9 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
       for (int q = 0; q < 4; ++q) {
         const int m = m0 + wm * 96 + i * 16 + q4 * 4 + q;
         if (m >= M) continue;
-        float* const dst = S > 1 ? g.part + ((int64_t)sl * M + m) * N
-                                 : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
-        const bool add = g.accumulate && S == 1;
+        float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
+                                  : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
+        const bool add = g.accumulate && !sliced;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const int col = n0 + wn * 128 + j * 16 + r16;
@@ -1120,12 +1183,13 @@ typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // ro
 __global__ void __launch_bounds__(256) k_sum_slices(const Args g) {
   int64_t c = (int64_t)g.cnt[0] - g.cnt_off;
   const int M = (int)(c < 0 ? 0 : (c > g.cnt_cap ? g.cnt_cap : c)), N = g.N;
-  const int S = __builtin_amdgcn_readfirstlane(pick_slices(M, N, g.K, g.ncu, g.part_elems));
+  const Plan pl = pick_plan(M, N, g.K, g.ncu, g.part_elems);
+  const int S = pl.S;
   if (S == 1) return;
-  const int64_t MN = (int64_t)M * N;
-  for (int m = blockIdx.x; m < M; m += gridDim.x) {
+  const int64_t MN = (int64_t)(M - pl.Mf) * N;
+  for (int m = pl.Mf + blockIdx.x; m < M; m += gridDim.x) {
     float* const dst = g.C + (int64_t)g.rows[g.rows_off + m] * g.ldc;
-    const float* const src = g.part + (int64_t)m * N;
+    const float* const src = g.part + (int64_t)(m - pl.Mf) * N;
     for (int n = threadIdx.x * 4; n < N; n += 1024) {  // N is a multiple of 8
       floatx4 v = *(const floatx4*)(src + n);
 #pragma unroll 4
@@ -1275,7 +1339,7 @@ hipError_t mfma_dz(const uint16_t* Hc, int64_t d, const uint16_t* W, int64_t V, 
 // (ld = Kp, whole 256-row panels whose rows past M (N) and columns past K hold
 // zeros); optional row scatter of C through rows[rows_off + m]; M or K can come
 // from the device counter.  With M from the counter and `part` (part_elems fp32
-// values of scratch), K may be split into slices (pick_slices; N a multiple of
+// values of scratch), K may be split into slices (pick_plan; N a multiple of
 // 4, no accumulation).
 hipError_t mfma_gemm_store(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb,
                            int64_t M, int64_t N, int64_t K, const int32_t* cnt, int64_t cnt_off,
@@ -1306,10 +1370,12 @@ hipError_t mfma_gemm_store(const uint16_t* A, int64_t lda, const uint16_t* B, in
     a.part = part;
     a.part_elems = part_elems;
   }
-  // a sliced result has at most kSliceRounds rounds of items
+  // slices: at most kSliceRounds rounds of items, or kTailRounds (of 384-row
+  // tiles; 1.5 times the 256-row ones) beyond the whole-K tiles
   const unsigned least = sliced ? (unsigned)(mf::kSliceRounds * ncu + 8) : 0u;
-  const unsigned g4 = std::max(grid_for384<mf::EPI_STORE>(M, N), least);
-  const unsigned g2 = std::max(grid_for<mf::EPI_STORE>(M, N), least);
+  const unsigned tail = sliced ? (unsigned)(mf::kTailRounds * ncu + mf::kMaxSlices * ((N + 255) / 256) + 8) : 0u;
+  const unsigned g4 = std::max(grid_for384<mf::EPI_STORE>(M, N) + tail, least);
+  const unsigned g2 = std::max(grid_for<mf::EPI_STORE>(M, N) + tail * 3 / 2 + 8, least);
   const bool can384 = fits384(lda, ldb, K, k_from_cnt) && force != 256;
   const bool only384 = can384 && (force == 384 || (!m_from_cnt && mf::prefer384(M, N, 1, ncu)));
   if (only384 || (can384 && m_from_cnt)) {

@@ -1,7 +1,8 @@
 """d_hidden of few rows through a bf16 head, whose K (the vocabulary) is split
 into slices: one row, rows around a 256-row tile, hidden sizes around a tile and
-small vocabularies (one slice), against float64 on the CPU; the same bits
-whichever tile RFT_GEMM_STORE_TILE fixes.
+small vocabularies (one slice), and many rows, of which only the last, partial
+round of tiles is cut; against float64; the same bits whichever tile
+RFT_GEMM_STORE_TILE fixes.
 
 Tolerance: dZ is rounded to bf16 (a relative 2^-9 per element; its fp32 value is
 off by the exponential's error, far below that), then a sum of V exact products
@@ -17,7 +18,7 @@ DEV = "cuda"
 
 @pytest.mark.parametrize("T,d,V", [(1, 8, 4096), (255, 264, 20000), (257, 248, 33000),
                                    (40, 1032, 9000), (700, 72, 40001), (1030, 512, 2049),
-                                   (130, 64, 65)])
+                                   (130, 64, 65), (18100, 4096, 2000), (17800, 4000, 1500)])
 def test_dh_slices(T, d, V, monkeypatch):
     print(f"[slices] T={T} d={d} V={V}", flush=True)
     g = torch.Generator().manual_seed(T + d + V)
@@ -40,14 +41,16 @@ def test_dh_slices(T, d, V, monkeypatch):
             monkeypatch.setenv("RFT_GEMM_STORE_TILE", tile)
         dH = torch.full((T, d), float("nan"), device=DEV)
         R.rft_ppo_clip_loss_bwd(tok, Hd, Wd, lse, c.to(DEV), d_hidden=dH)
-        outs.append(dH.cpu())
+        outs.append(dH)
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
-    h, w, n = H[m].double(), W.double(), int(m.sum())
+    m, lse, ids = m.to(DEV), lse.double(), ids.to(DEV)
+    c = c.to(DEV)
+    h, w, n = Hd[m].double(), Wd.double(), int(m.sum())
     z = h @ w.t()
     cm = c[m].double()[:, None]
-    p = torch.exp(z - lse.cpu()[m].double()[:, None])
+    p = torch.exp(z - lse[m][:, None])
     dz = -cm * p
-    dz[torch.arange(n), ids[m].long()] += c[m].double()
+    dz[torch.arange(n, device=DEV), ids[m].long()] += c[m].double()
     # d roundings of each logit and the exponential's, relative to p
     perr = (d + 64) * 2.0 ** -23 * (h.abs() @ w.abs().t()) + 64 * 2.0 ** -23 * (1 + z.abs())
     tol = (2.0 ** -8 + (V + 64) * 2.0 ** -23) * (dz.abs() @ w.abs()) + (cm.abs() * p * perr) @ w.abs()
