@@ -18,14 +18,17 @@
 // flight during the products; one barrier per step), and the fragments of
 // four K are read while the previous four's products run.  Measured (one pass
 // of forward, recompute, dH and dW; 1527 of 2048 rows valid, d = 1024, V =
-// 32000): 13.7 ms with the 64 x 64 vector-FMA tiles this replaces, 3.57 ms now;
-// the products run at 96-118 TFLOP/s (rocBLAS's largest fp32 product on the
-// same card: 153).
+// 32000): 13.7 ms with the 64 x 64 vector-FMA tiles this replaces, 3.50 ms now;
+// the products run at 100-120 TFLOP/s, the matrix pipe 60-82% busy at 2.2 GHz
+// (rocBLAS's largest fp32 product on the same card: 153).  Eight waves of 32 x 64
+// per tile and a wave priority by workgroup changed nothing.
 //
 // LDS stage: element (r, k) of an operand tile at k BT + (r ^ swz(k)).  Fragment
 // reads (16 rows at four consecutive k), the four-byte writes of a
 // K-contiguous operand (8 rows at eight k of the same k % 4) and the 16-byte
 // writes of a row-contiguous one each touch every bank once.
+#include <algorithm>
+
 #include "rft_internal.h"
 
 namespace rft {
@@ -60,6 +63,12 @@ struct Args {
   int kper; float* part; int64_t part_ld;
 };
 
+// exp(x), x <= 0, by the hardware exp2: its argument rounds once more than x
+// does, i.e. p is as exact as the difference it is taken of (results below 2^-126
+// are 0).  One instruction where the library's expf takes about 25 for each of a
+// wave's 64 x 64 values: 1% of a forward at K = 1024.
+__device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
+
 __device__ __forceinline__ int swz(int k) { return 16 * ((k + (k >> 2)) & 3) ^ 8 * ((k >> 4) & 1); }
 
 // Tile loader of a K-contiguous operand: lane l of wave w holds K chunk l / 8
@@ -69,7 +78,6 @@ template <int BT>
 struct LoadK {
   static constexpr int NI = BT / 32;
   const float* q[NI];
-  floatx4 v[NI];
   int row, kc;
   __device__ __forceinline__ void start(const Operand& o, int r0, int R, int k0, int) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -83,14 +91,14 @@ struct LoadK {
   }
   // whole K step inside K
   __device__ __forceinline__ bool whole(int k0, int K) const { return k0 + BK <= K; }
-  __device__ __forceinline__ void load(const Operand&, int, int) {
+  __device__ __forceinline__ void load(const Operand&, int, int, floatx4 (&v)[NI]) {
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       v[it] = (floatx4)(*(const f4u*)q[it]);
       q[it] += BK;
     }
   }
-  __device__ __forceinline__ void load_edge(const Operand&, int k0, int K) {
+  __device__ __forceinline__ void load_edge(const Operand&, int k0, int K, floatx4 (&v)[NI]) {
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
 #pragma unroll
@@ -98,7 +106,7 @@ struct LoadK {
       q[it] += BK;
     }
   }
-  __device__ __forceinline__ void put(float* s) const {
+  __device__ __forceinline__ void put(float* s, const floatx4 (&v)[NI]) const {
 #pragma unroll
     for (int it = 0; it < NI; ++it)
 #pragma unroll
@@ -115,7 +123,6 @@ struct LoadK {
 template <int BT>
 struct LoadR {
   static constexpr int NI = BT / 32, PER = 1024 / BT;
-  floatx4 v[NI];
   int64_t src[NI];
   int r4, kr, rbase, Rn;
   __device__ __forceinline__ void idx(const Operand& o, int k0, int K) {
@@ -136,13 +143,13 @@ struct LoadR {
   __device__ __forceinline__ bool whole(int k0, int K) const {
     return k0 + BK <= K && rbase - r4 + BT <= Rn;
   }
-  __device__ __forceinline__ void load(const Operand& o, int k0, int K) {
+  __device__ __forceinline__ void load(const Operand& o, int k0, int K, floatx4 (&v)[NI]) {
 #pragma unroll
     for (int it = 0; it < NI; ++it)
       v[it] = (floatx4)(*(const f4u*)(o.p + src[it] * o.ld + rbase));
     idx(o, k0 + BK, K);
   }
-  __device__ __forceinline__ void load_edge(const Operand& o, int k0, int K) {
+  __device__ __forceinline__ void load_edge(const Operand& o, int k0, int K, floatx4 (&v)[NI]) {
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const bool kv = k0 + kr + it * PER < K;
@@ -152,7 +159,7 @@ struct LoadR {
     }
     idx(o, k0 + BK, K);
   }
-  __device__ __forceinline__ void put(float* s) const {
+  __device__ __forceinline__ void put(float* s, const floatx4 (&v)[NI]) const {
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int k = kr + it * PER;
@@ -170,6 +177,9 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
   constexpr int BT = MIA == 4 ? 128 : 64;
   constexpr int WN = BT / 64;  // waves along N, 64 columns each
   constexpr int NR = MIA * 4;  // rows per lane
+  // steps whose loads are in flight: the small tile's products (1024 clocks per
+  // step) are shorter than a load
+  constexpr int PF = MIA == 4 ? 1 : 2;
   __shared__ __attribute__((aligned(16))) float lds[2][2][BK * BT];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -212,19 +222,26 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
     la.start(g.A, m0, M, k0, k1);
     lb.start(g.B, n0, NB, k0, k1);
   }
-  auto fetch = [&](int k) {
-    if (la.whole(k, k1)) la.load(g.A, k, k1); else la.load_edge(g.A, k, k1);
-    if (lb.whole(k, k1)) lb.load(g.B, k, k1); else lb.load_edge(g.B, k, k1);
+  floatx4 va[PF][Load<BT, AKC>::NI], vb[PF][Load<BT, BKC>::NI];
+  auto fetch = [&](int k, int p) {
+    if (la.whole(k, k1)) la.load(g.A, k, k1, va[p]); else la.load_edge(g.A, k, k1, va[p]);
+    if (lb.whole(k, k1)) lb.load(g.B, k, k1, vb[p]); else lb.load_edge(g.B, k, k1, vb[p]);
   };
-  if (k0 < k1) fetch(k0);
-  int st = 0;
-  for (int k = k0; k < k1; k += BK, st ^= 1) {
-    la.put(lds[st][0]);
-    lb.put(lds[st][1]);
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (k0 + p * BK < k1) fetch(k0 + p * BK, p);
+  for (int kb = k0; kb < k1; kb += PF * BK) {
+#pragma unroll
+   for (int p = 0; p < PF; ++p) {
+    const int k = kb + p * BK;
+    if (k >= k1) break;
+    const int st = PF == 1 ? ((k - k0) / BK) & 1 : p & 1;
+    la.put(lds[st][0], va[p]);
+    lb.put(lds[st][1], vb[p]);
     // this step's stage is complete; the other one is free once every wave is
     // past its products, i.e. at the next step's barrier
     __syncthreads();
-    if (k + BK < k1) fetch(k + BK);
+    if (k + PF * BK < k1) fetch(k + PF * BK, p);
     const float* As = lds[st][0];
     const float* Bs = lds[st][1];
     // the fragments of four K are read while the previous four's products run
@@ -250,6 +267,7 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
                                                            0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
+   }
   }
 
   // lane (r16, q4) holds rows m0 + wm + 16 i + 4 q4 + q, columns n0 + wn + 16 j + r16
@@ -274,7 +292,7 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
         const int n = n0 + wn + j * 16 + r16;
         const float z = acc[e >> 2][j][e & 3];
         if (n < N) {
-          const float p = expf(z - mx[e]);
+          const float p = exp_neg(z - mx[e]);
           sm[e] += p;
           um[e] += p * z;
           if (n == y) g.zy[g.rows_off + m] = z;
@@ -314,7 +332,7 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
           const float z = acc[e >> 2][j][e & 3];
           if (n < N)
             g.dz[(int64_t)m * g.ldz + n] =
-                n < g.Vvalid ? dlogit(c, eg, mu, expf(z - L), z, n == y) : 0.f;
+                n < g.Vvalid ? dlogit(c, eg, mu, exp_neg(z - L), z, n == y) : 0.f;
         }
       } else {
         float* dst = g.kper > 0
@@ -416,8 +434,10 @@ hipError_t f32_dz(const float* H, int64_t d, const float* W, int64_t V, int64_t 
 // slices whose partial sums go to `scratch` (scratch_elems fp32 values; 0 = no
 // split) and are added in slice order: enough slices for about eight tiles
 // per CU (the valid rows are fewer than Tc, and the last round is then a small
-// part), each of at least 128 K (a step of 32 K costs about 1.6 us while nothing
-// else runs, the sum's launch 4 us).
+// part), each of at least 128 K (a step of 32 K costs about 1 us while nothing
+// else runs, the sum's launch 4 us) and at most 64 (the sum reads them all:
+// 390 slices of 64 rows, d = 128, V = 50000 took 177 us for the backward, 64
+// take 85).
 hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int64_t d, int64_t Tc,
                   const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* scratch,
                   int64_t scratch_elems, hipStream_t s) {
@@ -433,7 +453,7 @@ hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int6
   a.C = dH; a.ldc = d; a.rows = rows; a.rows_off = c0; a.c_scatter = 1;
   const int64_t tiles = (Tc + 127) / 128 * ((d + 127) / 128);
   int64_t S = (8 * (int64_t)ncu + tiles - 1) / tiles;
-  S = S < V / 128 ? S : V / 128;
+  S = std::min<int64_t>(S, std::min<int64_t>(V / 128, 64));
   S = S < scratch_elems / (Tc * d) ? S : scratch_elems / (Tc * d);
   if (S < 2 || tiles >= ncu) return f3::launch<f3::EPI_STORE, true, false>(a, Tc, d, 1, s);
   const int64_t kper = ((V + S - 1) / S + f3::BK - 1) / f3::BK * f3::BK;
