@@ -361,6 +361,26 @@ __device__ __forceinline__ uint32_t pk_f16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, f16x2_t));
 }
 
+// The fp32-store GEMMs take each 16 x 16 tile transposed (the operands of the
+// matrix instruction change places, the products and their order do not), so a
+// lane holds row r16 of the tile and four consecutive columns, and stores them as
+// 16 bytes: a quarter of the store instructions, which weigh most in d_weight of
+// a micro-batch (few K steps per tile; SFT calls on 1152 rows of the 7B shape 4.61
+// -> 4.53 ms, on smaller heads up to 4%).  acc[j]: columns col + 16 j .. + 3; N is a multiple of 8, the rows of C need no alignment.
+typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_row(const floatx4 (&acc)[8], float* dst, int col, int N,
+                                          bool add) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int c = col + j * 16;
+    if (c < N) {
+      floatx4 v = acc[j];
+      if (add) v += (floatx4)*(const floatx4_a4*)(dst + c);
+      *(floatx4_a4*)(dst + c) = v;
+    }
+  }
+}
+
 template <int EPI>
 __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
   constexpr bool kStats = EPI == EPI_STATS || EPI == EPI_STATS_Y;
@@ -513,7 +533,9 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
           for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-              acc4[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][j], 0, 0, 0);
+              acc4[i][j] = EPI == EPI_STORE
+                  ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc4[i][j], 0, 0, 0)
+                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][j], 0, 0, 0);
         }
       }
       // Before the barrier: this wave's loads of the next stage have landed
@@ -740,33 +762,19 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
         __syncthreads();
         stage_copy_out_blk<STG_PITCH_T>(st, g.dzt + (int64_t)n0 * g.ldzt + (int64_t)m0 * BM, tid);
       }
-    } else {  // EPI_STORE
+    } else {  // EPI_STORE (transposed tiles: see store_row)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int rl = wm * 64 + i * 16 + q4 * 4 + q;
-          const int m = m0 + rl;
-          if (m >= M) continue;
-          float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
-                                    : g.C + (int64_t)rp_i[rl] * g.ldc;
-          const bool add = g.accumulate && !sliced;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int col = n0 + wn * 128 + j * 16 + r16;
-            if (col < N) {
-              float v = acc4[i][j][q];
-              if (add) v += dst[col];
-              dst[col] = v;
-            }
-          }
-        }
+        const int rl = wm * 64 + i * 16 + r16, m = m0 + rl;
+        if (m >= M) continue;
+        float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
+                                  : g.C + (int64_t)rp_i[rl] * g.ldc;
+        store_row(acc4[i], dst, n0 + wn * 128 + q4 * 4, N, g.accumulate && !sliced);
       }
     }
   }
 }
-
 
 // The GEMM on a 384 x 256 workgroup tile for tile-blocked operands: the
 // fp32 store of the step's dH and dW (EPI_STORE), the fused step's forward
@@ -926,7 +934,9 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         acc4[i][h * 4 + j] =
-            __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][h * 4 + j], 0, 0, 0);
+            EPI == EPI_STORE
+                ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc4[i][h * 4 + j], 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc4[i][h * 4 + j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
     barrier_lds();
@@ -957,27 +967,16 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   if (!late) barrier_lds();
   // element q of tile (i, j) is row wm*96 + i*16 + q4*4 + q and column
   // wn*128 + j*16 + r16 of the workgroup tile
+  // (EPI_STORE: of row wm*96 + i*16 + r16 and column wn*128 + j*16 + q4*4 + q)
   if constexpr (EPI == EPI_STORE) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = m0 + wm * 96 + i * 16 + q4 * 4 + q;
-        if (m >= M) continue;
-        float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
-                                  : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
-        const bool add = g.accumulate && !sliced;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int col = n0 + wn * 128 + j * 16 + r16;
-          if (col < N) {
-            float v = acc4[i][j][q];
-            if (add) v += dst[col];
-            dst[col] = v;
-          }
-        }
-      }
+      const int m = m0 + wm * 96 + i * 16 + r16;
+      if (m >= M) continue;
+      float* const dst = sliced ? g.part + ((int64_t)sl * (M - pl.Mf) + (m - pl.Mf)) * N
+                                : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
+      store_row(acc4[i], dst, n0 + wn * 128 + q4 * 4, N, g.accumulate && !sliced);
     }
   } else {
     // Forward: k_gemm's EPI_STATS(_Y) arithmetic per row and 256-column tile
@@ -1177,7 +1176,6 @@ __global__ void __launch_bounds__(NT, 1) k_gemm384(const Args g) {
   }
 }
 
-typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // rows of the caller's buffer
 // C[rows[rows_off + m], n] = the sum over the slices of part, in slice order
 // (nothing to do when the GEMM took one slice).
 __global__ void __launch_bounds__(256) k_sum_slices(const Args g) {
