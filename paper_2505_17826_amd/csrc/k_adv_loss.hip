@@ -2,7 +2,6 @@
 // their fixed-order fp64 reduction, and the merge of the per-tile
 // log-sum-exp partials into per-token log-prob / entropy / lse.
 #include "rft_internal.h"
-#include "tokens_device.h"
 
 namespace rft {
 
@@ -572,8 +571,7 @@ hipError_t launch_loss_reduce(const LossPartial* parts, int64_t n, LossPartial* 
 }
 
 // A handful of rows (at most kLossThreads) whose statistics are in P parts each:
-// the token bookkeeping, the merge, the row terms and the loss statistics in one
-// workgroup.  Every part is read before the terms (lse, c, e, entropy, [T] each)
+// the merge, the row terms and the loss statistics in one workgroup.  Every part is read before the terms (lse, c, e, entropy, [T] each)
 // take its place.
 template <int P>
 __global__ void __launch_bounds__(kLossThreads) k_few_terms(
@@ -588,11 +586,13 @@ __global__ void __launch_bounds__(kLossThreads) k_few_terms(
   for (int i = 0; i < P; ++i)
     v[i] = on ? ((const RowStats*)scratch)[t * P + i] : RowStats{0.f, 1.f, 0.f};
   int y = on ? tok.token_ids[t] : -1;
+  const int i = on ? m.row_seq[m.kidx[t]] : 0;
+  const float A = on ? adv[i] : 0.f;
+  const int n = on ? m.n_i[i] : 0;
   const bool ok = y >= 0 && (int64_t)y < V;
   const float zy = ok ? logits[(int64_t)t * V + y] : 0.f;
   const float od = on ? old[t] : 0.f, rf0 = on && ref ? ref[t] : 0.f;
-  tokmeta_small<kLossThreads>(tok, m);
-  __syncthreads();
+  __syncthreads();  // every part is read
   LossPartial p = RFT_ZERO_PARTIAL;
   if (t < T) {
     float L = 0.f, H = 0.f, lp = 0.f, g = 0.f, e = 0.f;
@@ -604,9 +604,8 @@ __global__ void __launch_bounds__(kLossThreads) k_few_terms(
       if (!ok) {
         p.bad = 1;
       } else {
-        const int i = m.row_seq[m.kidx[t]];
         const bool ex = c.is_expert && c.is_expert[i];
-        g = row_loss(lp, od, ref ? rf0 : lp, adv[i], m.n_i[i], ex, m.meta, (double)H, c, p, &e);
+        g = row_loss(lp, od, ref ? rf0 : lp, A, n, ex, m.meta, (double)H, c, p, &e);
       }
     }
     logp[t] = lp;

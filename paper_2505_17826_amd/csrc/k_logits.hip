@@ -17,6 +17,7 @@
 // same chunks of the row in the same order, so the statistics-only,
 // d_logits-only and fused kernels agree bit for bit.
 #include "rft_internal.h"
+#include "tokens_device.h"
 
 namespace rft {
 namespace lg {
@@ -242,17 +243,22 @@ __global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ log
 
 // ---- a handful of long rows: one workgroup per row leaves CUs idle, and a CU
 // reads a row at its own rate (about 40 us for 600 KB read and written), so a
-// row is cut into P = 2, 4 or 8 parts of 8 / P waves: this kernel, the row terms
-// of all rows in one workgroup (launch_few_terms), then k_logits_bwd with P
+// row is cut into P = 2, 4 or 8 parts of 8 / P waves: this kernel (and the token
+// bookkeeping in one workgroup more), the row terms of all rows in one workgroup
+// (launch_few_terms), then k_logits_bwd with P
 // workgroups per row, which finds the logits in the last-level cache.  Whole
-// call at V = 151936: 128 rows 47 -> 45 us, 64 rows 48 -> 36, 16 rows 46 -> 29.
+// call at V = 151936: 128 rows 47 -> 42 us, 64 rows 48 -> 34, 16 rows 46 -> 26.
 template <int P>
 __global__ void __launch_bounds__(NT / P) k_logits_part(const float* __restrict__ logits, int64_t V,
-                                                         const uint8_t* __restrict__ mask,
+                                                         const rft_tokens tok, TokMeta m,
                                                          RowStats* __restrict__ part) {
   __shared__ RowStats sh[NT / P / 64 + 1];
   const int64_t t = blockIdx.x / P;
-  if (!mask[t]) return;
+  if (t == tok.T) {  // one workgroup more for the token bookkeeping
+    tokmeta_small<NT / P>(tok, m);
+    return;
+  }
+  if (!tok.mask[t]) return;
   const int vt = (int)(blockIdx.x % P) * (NT / P) + threadIdx.x;
   const float* z = logits + t * V;
   RowStats r = {-INFINITY, 0.f, 0.f};
@@ -582,15 +588,15 @@ hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const
   // the parts (12 bytes each) take the room of the T row partials and of the
   // one after them (workspaces are whole multiples of 256 bytes)
   while (lp > 0 && (tok.T << lp) * (int64_t)sizeof(RowStats) > (char*)parts2 - (char*)parts + 256) --lp;
-  // few rows: launch_few_terms does the bookkeeping
-  const bool few = lp > 0 && tok.n_seq <= kFewSeq;
+  // few rows: k_logits_part does the bookkeeping (T <= 8 threads of a part)
+  const bool few = lp > 0 && tok.n_seq <= kFewSeq && tok.T <= 8 * (lg::NT >> lp);
   if (!few && (e = launch_tokmeta(tok, m, s)) != hipSuccess) return e;
   if (few) {
     RowStats* const part = (RowStats*)parts;
-    const unsigned nb = (unsigned)(tok.T << lp);
-    if (lp == 3) lg::k_logits_part<8><<<nb, lg::NT / 8, 0, s>>>(logits, V, tok.mask, part);
-    else if (lp == 2) lg::k_logits_part<4><<<nb, lg::NT / 4, 0, s>>>(logits, V, tok.mask, part);
-    else lg::k_logits_part<2><<<nb, lg::NT / 2, 0, s>>>(logits, V, tok.mask, part);
+    const unsigned nb = (unsigned)(tok.T << lp) + 1;
+    if (lp == 3) lg::k_logits_part<8><<<nb, lg::NT / 8, 0, s>>>(logits, V, tok, m, part);
+    else if (lp == 2) lg::k_logits_part<4><<<nb, lg::NT / 4, 0, s>>>(logits, V, tok, m, part);
+    else lg::k_logits_part<2><<<nb, lg::NT / 2, 0, s>>>(logits, V, tok, m, part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_few_terms(logits, tok, m, V, 1 << lp, old, ref, adv, c, logp, ent, lse, grad,
                               parts, st, s)) != hipSuccess)
