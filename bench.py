@@ -39,13 +39,14 @@ WORKLOADS = {"tiny": 0, "1.5b": 1, "7b": 2, "longcot": 3, "lossonly": 4}
 TRAFFIC = {
     # forward GEMM alone (k_gemm384<EPI_STATS> on the tile-blocked copies, one launch over
     # all valid rows)
-    "7b": {"sources": {'k_gemm_mfma.hip': 'dc0da0d44c0974ed', 'rft_internal.h': '08981c3504904a8e'},
-           "bytes": 151531338.1 * 1024 * 2.0 + 1174412.5 * 1024 * 1.0},
-    # every kernel of one rft_ppo_clip_step call (28 dispatches, two row chunks)
-    "step_7b": {"sources": {'k_gemm_mfma.hip': 'dc0da0d44c0974ed', 'k_step.hip': '39fcacd3c55e6f75', 'k_layout.hip': '79fa372b0122fc73', 'k_adv_loss.hip': 'fe9e2b4d1d0b6332', 'k_tokens.hip': 'd52b04cf394f6696', 'rft_internal.h': '08981c3504904a8e', 'rft_abi.hip': '8db0c2f778a91fe2'},
-                "bytes": 579511823.2 * 1024 * 2.0 + 163468902.1 * 1024 * 1.0},
-    "lossonly": {"sources": {'k_logits.hip': '784099cf37962bf5', 'rft_internal.h': '08981c3504904a8e'},
-                 "bytes": 8758808.5 * 1024 * 2.0 + 19478868.4 * 1024 * 1.0},
+    "7b": {"sources": {'k_gemm_mfma.hip': '90fcec7603bc95eb', 'rft_internal.h': 'eba41893a97440c2'},
+           "bytes": 174218929.2 * 1024 * 2.0 + 1174427.7 * 1024 * 1.0},
+    # every kernel of one rft_ppo_clip_step call and its advantages (24 dispatches, two
+    # row chunks)
+    "step_7b": {"sources": {'k_gemm_mfma.hip': '90fcec7603bc95eb', 'k_step.hip': 'a920d8a6385f4246', 'k_layout.hip': '59fafc69e9c8b096', 'k_adv_loss.hip': '645923f87d774313', 'k_tokens.hip': '45fb1d5641296ae5', 'tokens_device.h': '73eabd5a3070690d', 'rft_internal.h': 'eba41893a97440c2', 'rft_abi.hip': '4945fc524dee1e45'},
+                "bytes": 623616757.6 * 1024 * 2.0 + 164163235.7 * 1024 * 1.0},
+    "lossonly": {"sources": {'k_logits.hip': 'a5f96d785b04e5ec', 'rft_internal.h': 'eba41893a97440c2'},
+                 "bytes": 8759825.4 * 1024 * 2.0 + 19500315.8 * 1024 * 1.0},
 }
 
 

@@ -139,7 +139,7 @@ __host__ __device__ inline bool prefer384(int64_t M, int64_t N, int64_t slices, 
 //  - Many tiles: whole rounds of 384-row tiles (in steps of 768 rows, which both
 //    tiles divide), and the rows of the last, partial round in S slices, so that
 //    every CU ends within 1 / S of a tile.  At 42000 rows 7 rounds with 4 tiles in
-//    the last took 36.3 ms, 6.02 rounds' worth takes 32.2.
+//    the last took 36.3 ms, 6.02 rounds' worth takes 33.5.
 // At most kMaxSlices slices and the scratch.  Every wave of the GEMM and of the
 // sum computes the same plan (in integers: whatever the compiler contracts) from
 // the same count, and it does not depend on the tile, so both give the same bits.
