@@ -86,25 +86,32 @@ __device__ __forceinline__ void acc1(RowStats& r, float z) {
 }
 
 // Workgroup reduction of the per-thread online partials, in a fixed order: a
-// binary tree over the waves, so that a row cut into 2, 4 or 8 parts of whole
-// waves (k_logits_part) ends with the same bits.
+// binary tree over the waves (lane i of the first wave holds wave i's partial;
+// lane 0 ends with the pairs of tree_merge, in its order), so that a row cut
+// into 2, 4 or 8 parts of whole waves (k_logits_part) ends with the same bits.
+// Six registers: with all the waves' partials in one thread the one-workgroup
+// kernel, which holds 224 registers of the row here, spilled four.
 template <int NTH = NT>
 __device__ RowStats block_stats(RowStats r, RowStats* sh) {
+  constexpr int NW = NTH / 64;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   float M = wave_max_f(r.m);
   float sc = (r.s > 0.f) ? __builtin_amdgcn_exp2f((r.m - M) * kLog2e) : 0.f;
   float s = wave_sum_f(r.s * sc), u = wave_sum_f(r.u * sc);
   if (lane == 0) sh[w] = RowStats{M, s, u};
   __syncthreads();
-  if (threadIdx.x == 0) {
-    RowStats v[NTH / 64];
+  if (threadIdx.x < NW) {
+    RowStats v = sh[threadIdx.x];
 #pragma unroll
-    for (int i = 0; i < NTH / 64; ++i) v[i] = sh[i];
-    tree_merge(v);
-    sh[NTH / 64] = v[0];
+    for (int o = 1; o < NW; o <<= 1) {
+      const float m2 = __shfl_xor(v.m, o, 64), s2 = __shfl_xor(v.s, o, 64);
+      const float u2 = __shfl_xor(v.u, o, 64);
+      lse_merge(v.m, v.s, v.u, m2, s2, u2);
+    }
+    if (threadIdx.x == 0) sh[NW] = v;
   }
   __syncthreads();
-  RowStats out = sh[NTH / 64];
+  RowStats out = sh[NW];
   __syncthreads();
   return out;
 }
