@@ -23,6 +23,10 @@
 // (rocBLAS's largest fp32 product on the same card: 153).  Eight waves of 32 x 64
 // per tile and a wave priority by workgroup changed nothing.
 //
+// The epilogues take the library's exponential: the hardware exp2 of the rounded
+// x log2(e) would save 1% of a step (3.32 against 3.35 ms, 2048 rows, d = 1024, V =
+// 32000) but is off by up to 15 half-ulps at x = -15, all with one sign.
+//
 // LDS stage: element (r, k) of an operand tile at k BT + (r ^ swz(k)).  Fragment
 // reads (16 rows at four consecutive k), the four-byte writes of a
 // K-contiguous operand (8 rows at eight k of the same k % 4) and the 16-byte
@@ -62,12 +66,6 @@ struct Args {
   // kper) and stores its sum to part + s part_ld (rows of N, compact); 0 = no split
   int kper; float* part; int64_t part_ld;
 };
-
-// exp(x), x <= 0, by the hardware exp2: its argument rounds once more than x
-// does, i.e. p is as exact as the difference it is taken of (results below 2^-126
-// are 0).  One instruction where the library's expf takes about 25 for each of a
-// wave's 64 x 64 values: 1% of a forward at K = 1024.
-__device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 
 __device__ __forceinline__ int swz(int k) { return 16 * ((k + (k >> 2)) & 3) ^ 8 * ((k >> 4) & 1); }
 
@@ -292,7 +290,7 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
         const int n = n0 + wn + j * 16 + r16;
         const float z = acc[e >> 2][j][e & 3];
         if (n < N) {
-          const float p = exp_neg(z - mx[e]);
+          const float p = expf(z - mx[e]);
           sm[e] += p;
           um[e] += p * z;
           if (n == y) g.zy[g.rows_off + m] = z;
@@ -332,7 +330,7 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
           const float z = acc[e >> 2][j][e & 3];
           if (n < N)
             g.dz[(int64_t)m * g.ldz + n] =
-                n < g.Vvalid ? dlogit(c, eg, mu, exp_neg(z - L), z, n == y) : 0.f;
+                n < g.Vvalid ? dlogit(c, eg, mu, expf(z - L), z, n == y) : 0.f;
         }
       } else {
         float* dst = g.kper > 0
