@@ -317,6 +317,11 @@ rft_status rft_ppo_clip_loss_fwd(const rft_tokens* tok, int64_t V, const float* 
  * read K-contiguous operands: about 4 Vpad + 2 d bytes per chunk row).
  * lse and grad_logp [T] are normally the outputs of rft_token_logprobs and
  * rft_ppo_clip_loss_fwd.
+ * fp32, few rows: d_hidden is summed over slices of the vocabulary, whose
+ * partial sums (at most V d values) the recommended workspace has room for when
+ * it holds every row in one chunk.  Without that room a call that accumulates
+ * d_weight, or one of several chunks, takes longer; for the same chunks
+ * d_hidden is the same bit for bit, also with and without accumulate_dw.
  * Errors: as rft_token_logprobs. */
 rft_status rft_ppo_clip_loss_bwd(const rft_tokens* tok, const void* hidden, const void* weight,
                                  int dtype, int64_t d, int64_t V, const float* lse,

@@ -63,7 +63,8 @@ struct Args {
   float* dz; int64_t ldz; int64_t Vvalid;
   float* C; int64_t ldc; int accumulate; int c_scatter;
   // EPI_STORE over splits of K: slice s = blockIdx.y covers K [s kper, s kper +
-  // kper) and stores its sum to part + s part_ld (rows of N, compact); 0 = no split
+  // kper) and stores its sum to part + s part_ld (rows of N, compact); 0 = no split.
+  // SEQ: one workgroup walks the slices and adds their sums itself (part unused)
   int kper; float* part; int64_t part_ld;
 };
 
@@ -170,8 +171,12 @@ template <int BT, bool KC> struct Load : LoadK<BT> {};
 template <int BT> struct Load<BT, false> : LoadR<BT> {};
 
 // MIA = 4: 128 x 128 tile; MIA = 1: 64 x 64.  AKC / BKC: operand K-contiguous.
-template <int EPI, int MIA, bool AKC, bool BKC>
+// SEQ: the slices of K in turn, each from zero, their sums added in order: the
+// bits of the split launch and k_sum_slices, with no room for partial sums
+// (64 x 64 tile only: a second set of a 128 x 128 tile's sums does not fit).
+template <int EPI, int MIA, bool AKC, bool BKC, bool SEQ = false>
 __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
+  static_assert(!SEQ || MIA == 1, "see above");
   constexpr int BT = MIA == 4 ? 128 : 64;
   constexpr int WN = BT / 64;  // waves along N, 64 columns each
   constexpr int NR = MIA * 4;  // rows per lane
@@ -204,7 +209,8 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
   const int mt = (int)(mfast ? t % nTm : t / nTn), nt = (int)(mfast ? t / nTm : t % nTn);
   const int m0 = mt * BT, n0 = nt * BT;
   int k0 = 0, k1 = K;
-  if (EPI == EPI_STORE && g.kper > 0) {
+  const bool split = EPI == EPI_STORE && !SEQ && g.kper > 0;
+  if (split) {
     k0 = (int)blockIdx.y * g.kper;
     k1 = k0 + g.kper < K ? k0 + g.kper : K;
   }
@@ -214,6 +220,14 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
   for (int i = 0; i < MIA; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  floatx4 tot[SEQ ? MIA : 1][SEQ ? 4 : 1];  // SEQ: the sum of the slices before this one
+  if constexpr (SEQ) {
+#pragma unroll
+    for (int i = 0; i < MIA; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) tot[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+  }
+  int kend = SEQ ? g.kper : 0;  // end of the slice (whole K steps)
   Load<BT, AKC> la;
   Load<BT, BKC> lb;
   if (k0 < k1) {
@@ -233,6 +247,18 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
    for (int p = 0; p < PF; ++p) {
     const int k = kb + p * BK;
     if (k >= k1) break;
+    if constexpr (SEQ) {
+      if (k == kend) {
+        kend += g.kper;
+#pragma unroll
+        for (int i = 0; i < MIA; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            tot[i][j] += acc[i][j];
+            acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+          }
+      }
+    }
     const int st = PF == 1 ? ((k - k0) / BK) & 1 : p & 1;
     la.put(lds[st][0], va[p]);
     lb.put(lds[st][1], vb[p]);
@@ -266,6 +292,13 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
       __builtin_amdgcn_sched_barrier(0);
     }
    }
+  }
+
+  if constexpr (SEQ) {
+#pragma unroll
+    for (int i = 0; i < MIA; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = tot[i][j] + acc[i][j];
   }
 
   // lane (r16, q4) holds rows m0 + wm + 16 i + 4 q4 + q, columns n0 + wn + 16 j + r16
@@ -333,10 +366,10 @@ __global__ void __launch_bounds__(NT, 2) k_gemm_f32(const Args g) {
                 n < g.Vvalid ? dlogit(c, eg, mu, expf(z - L), z, n == y) : 0.f;
         }
       } else {
-        float* dst = g.kper > 0
+        float* dst = split
                          ? g.part + (int64_t)blockIdx.y * g.part_ld + (int64_t)m * N
                          : g.C + (int64_t)(g.c_scatter ? g.rows[g.rows_off + m] : m) * g.ldc;
-        const bool add = g.accumulate && g.kper == 0;
+        const bool add = g.accumulate && !split;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int n = n0 + wn + j * 16 + r16;
@@ -378,19 +411,19 @@ static bool tile128(int64_t M, int64_t N, int64_t splits, int64_t ncu) {
   return (big + ncu - 1) / ncu * 400 <= (small + ncu - 1) / ncu * 115;
 }
 
-template <int EPI, bool AKC, bool BKC>
+template <int EPI, bool AKC, bool BKC, bool SEQ = false>
 static hipError_t launch(const Args& a, int64_t Mcap, int64_t N, int splits, hipStream_t s) {
   int ncu = 0;
   hipError_t e = cu_count(&ncu);
   if (e != hipSuccess) return e;
-  const bool big = tile128(Mcap, N, splits, ncu);
+  const bool big = !SEQ && tile128(Mcap, N, splits, ncu);
   const int64_t bt = big ? 128 : 64;
   const int64_t tiles = (Mcap + bt - 1) / bt * ((N + bt - 1) / bt);
   // at most 2^20 workgroups in x (a launch holds fewer than 2^32 work-items there)
   const int64_t nb = (tiles + 7) / 8 * 8, bx = nb < (1 << 20) ? nb : (1 << 20);
   const dim3 grid((unsigned)bx, (unsigned)splits, (unsigned)((nb + bx - 1) / bx));
   if (big) k_gemm_f32<EPI, 4, AKC, BKC><<<grid, NT, 0, s>>>(a);
-  else k_gemm_f32<EPI, 1, AKC, BKC><<<grid, NT, 0, s>>>(a);
+  else k_gemm_f32<EPI, 1, AKC, BKC, SEQ><<<grid, NT, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -429,16 +462,33 @@ hipError_t f32_dz(const float* H, int64_t d, const float* W, int64_t V, int64_t 
 
 // dH[rows[c0 + m], :] = dZ[m, :] . W for the chunk's rows.  With few rows the
 // tiles of [Tc, d] leave CUs idle while K = V is long, so K is split into
-// slices whose partial sums go to `scratch` (scratch_elems fp32 values; 0 = no
-// split) and are added in slice order: enough slices for about eight tiles
+// slices whose partial sums go to `part` and are added in slice order: enough
+// slices for about eight tiles
 // per CU (the valid rows are fewer than Tc, and the last round is then a small
 // part), each of at least 128 K (a step of 32 K costs about 1 us while nothing
 // else runs, the sum's launch 4 us) and at most 64 (the sum reads them all:
 // 390 slices of 64 rows, d = 128, V = 50000 took 177 us for the backward, 64
-// take 85).
+// take 85), their sums no larger than d_weight.  1 = no split.
+static int64_t dh_slices(int64_t Tc, int64_t d, int64_t V, int64_t ncu) {
+  const int64_t tiles = (Tc + 127) / 128 * ((d + 127) / 128);
+  if (tiles >= ncu) return 1;
+  const int64_t S = std::min<int64_t>((8 * ncu + tiles - 1) / tiles, std::min<int64_t>(V / 128, 64));
+  return std::max<int64_t>(1, std::min<int64_t>(S, V / Tc));
+}
+
+// fp32 values that the partial sums of chunks of Tc rows take (a workspace is
+// sized without a device: for the 256 CUs of the card; fewer take fewer slices).
+int64_t f32_dh_part_elems(int64_t Tc, int64_t d, int64_t V) {
+  const int64_t S = dh_slices(Tc, d, V, 256);
+  return S > 1 ? S * Tc * d : 0;
+}
+
+// part: room for f32_dh_part_elems(Tc, d, V) values, or nullptr: the workgroups
+// then walk the same slices one after the other, on as few CUs as there are
+// tiles, and the sums are the same bit for bit.
 hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int64_t d, int64_t Tc,
-                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* scratch,
-                  int64_t scratch_elems, hipStream_t s) {
+                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* part,
+                  hipStream_t s) {
   if (Tc <= 0) return hipSuccess;
   int ncu = 0;
   hipError_t e = cu_count(&ncu);
@@ -449,19 +499,17 @@ hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int6
   a.M = (int)Tc; a.N = (int)d; a.K = (int)V;
   a.cnt = cnt; a.cnt_off = c0; a.cnt_cap = Tc; a.m_from_cnt = 1;
   a.C = dH; a.ldc = d; a.rows = rows; a.rows_off = c0; a.c_scatter = 1;
-  const int64_t tiles = (Tc + 127) / 128 * ((d + 127) / 128);
-  int64_t S = (8 * (int64_t)ncu + tiles - 1) / tiles;
-  S = std::min<int64_t>(S, std::min<int64_t>(V / 128, 64));
-  S = S < scratch_elems / (Tc * d) ? S : scratch_elems / (Tc * d);
-  if (S < 2 || tiles >= ncu) return f3::launch<f3::EPI_STORE, true, false>(a, Tc, d, 1, s);
+  int64_t S = dh_slices(Tc, d, V, std::min(ncu, 256));
+  if (S < 2) return f3::launch<f3::EPI_STORE, true, false>(a, Tc, d, 1, s);
   const int64_t kper = ((V + S - 1) / S + f3::BK - 1) / f3::BK * f3::BK;
   S = (V + kper - 1) / kper;
   a.kper = (int)kper;
-  a.part = scratch;
+  if (!part) return f3::launch<f3::EPI_STORE, true, false, true>(a, Tc, d, 1, s);
+  a.part = part;
   a.part_ld = Tc * d;
   if ((e = f3::launch<f3::EPI_STORE, true, false>(a, Tc, d, (int)S, s)) != hipSuccess) return e;
   f3::k_sum_slices<<<(unsigned)(Tc < 16384 ? Tc : 16384), 256, 0, s>>>(
-      scratch, (int)S, a.part_ld, d, cnt, c0, Tc, rows, c0, dH, d);
+      part, (int)S, a.part_ld, d, cnt, c0, Tc, rows, c0, dH, d);
   return hipGetLastError();
 }
 

@@ -251,6 +251,17 @@ int64_t bwd_tc_max(const rft_tokens& tok, int dtype) {
   return t < kMaxTc ? t : kMaxTc;
 }
 
+// fp32: room for d_hidden's partial sums after the workspace of chunks of Tc
+// rows.  The recommended workspace of one chunk of every row includes it, the
+// required one does not, and it never makes a chunk smaller.
+size_t bwd_part_bytes(int64_t d, int64_t V, int dtype, int64_t Tc) {
+  return dtype == RFT_F32 ? (size_t)round_up(f32_dh_part_elems(Tc, d, V) * 4, 256) : 0;
+}
+size_t bwd_bytes(const rft_tokens& tok, int64_t d, int64_t V, int dtype, int64_t Tc) {
+  const size_t b = carve_bwd(nullptr, tok, d, V, dtype, Tc).bytes;
+  return Tc == bwd_tc_max(tok, dtype) ? b + bwd_part_bytes(d, V, dtype, Tc) : b;
+}
+
 // largest row chunk (a multiple of the alignment) whose workspace fits, 0 if none
 int64_t bwd_tc_for(const rft_tokens& tok, int64_t d, int64_t V, int dtype, size_t ws_bytes) {
   int64_t a = bwd_align(dtype);
@@ -322,14 +333,19 @@ int64_t step_tc_for(const rft_tokens& tok, int64_t d, int64_t V, size_t ws_bytes
 
 // fp32 step: the three calls share the front of the workspace; the entropy
 // bonus coefficients [T] follow it.
-size_t step_f32_front(const rft_tokens& tok, int64_t d, int64_t V, int64_t Tc) {
+size_t step_f32_front(const rft_tokens& tok, int64_t d, int64_t V, size_t bwd) {
   size_t a = carve_fwd(nullptr, tok, d, V, RFT_F32).bytes;
   size_t b = carve_loss(nullptr, tok, false).bytes;
-  size_t c = carve_bwd(nullptr, tok, d, V, RFT_F32, Tc).bytes;
-  return (size_t)round_up((int64_t)std::max(a, std::max(b, c)), 256);
+  return (size_t)round_up((int64_t)std::max(a, std::max(b, bwd)), 256);
+}
+size_t step_f32_tail(const rft_tokens& tok) {
+  return (size_t)round_up((tok.T > 0 ? tok.T : 1) * 4, 256);
 }
 size_t step_f32_bytes(const rft_tokens& tok, int64_t d, int64_t V, int64_t Tc) {
-  return step_f32_front(tok, d, V, Tc) + (size_t)round_up((tok.T > 0 ? tok.T : 1) * 4, 256);
+  return step_f32_front(tok, d, V, bwd_bytes(tok, d, V, RFT_F32, Tc)) + step_f32_tail(tok);
+}
+size_t step_f32_min_front(const rft_tokens& tok, int64_t d, int64_t V) {
+  return step_f32_front(tok, d, V, carve_bwd(nullptr, tok, d, V, RFT_F32, kF32Align).bytes);
 }
 
 rft_status check_fused_logits(const char* fn, const rft_tokens* tok, const float* logits, int64_t V,
@@ -425,7 +441,7 @@ size_t rft_workspace_bytes(int op, const rft_tokens* tok, int64_t d, int64_t V, 
       if ((dtype != RFT_F32 && dtype != RFT_BF16) || d < 1) return 0;
       int64_t tc = bwd_tc_max(*tok, dtype);
       if (tc > kRecommendTc) tc = kRecommendTc;
-      return carve_bwd(nullptr, *tok, d, V, dtype, tc).bytes;
+      return bwd_bytes(*tok, d, V, dtype, tc);
     }
     case RFT_OP_PPO_STEP: {
       if ((dtype != RFT_F32 && dtype != RFT_BF16) || d < 1) return 0;
@@ -445,7 +461,7 @@ size_t rft_workspace_min_bytes(int op, const rft_tokens* tok, int64_t d, int64_t
     if (dtype != RFT_F32 && dtype != RFT_BF16) return 0;
     if (op == RFT_OP_PPO_STEP)
       return dtype == RFT_BF16 ? carve_step(nullptr, *tok, d, V, kBf16Align).bytes
-                               : step_f32_bytes(*tok, d, V, bwd_align(dtype));
+                               : step_f32_min_front(*tok, d, V) + step_f32_tail(*tok);
     return carve_bwd(nullptr, *tok, d, V, dtype, bwd_align(dtype)).bytes;
   }
   if (op == RFT_OP_TOKEN_LOGPROBS) {
@@ -467,7 +483,7 @@ size_t rft_workspace_bytes_rows(int op, const rft_tokens* tok, int64_t d, int64_
   if (op == RFT_OP_PPO_STEP)
     return dtype == RFT_BF16 ? carve_step(nullptr, *tok, d, V, tc).bytes
                              : step_f32_bytes(*tok, d, V, tc);
-  return carve_bwd(nullptr, *tok, d, V, dtype, tc).bytes;
+  return bwd_bytes(*tok, d, V, dtype, tc);
 }
 
 int64_t rft_chunk_rows(int op, const rft_tokens* tok, int64_t d, int64_t V, int dtype,
@@ -478,10 +494,10 @@ int64_t rft_chunk_rows(int op, const rft_tokens* tok, int64_t d, int64_t V, int 
   if (op == RFT_OP_PPO_STEP) {
     if (dtype == RFT_BF16) return step_tc_for(*tok, d, V, ws_bytes);
     // fp32: the separate backward runs in the front of the workspace
-    const int64_t tail = round_up((tok->T > 0 ? tok->T : 1) * 4, 256);
+    const int64_t tail = (int64_t)step_f32_tail(*tok);
     if ((int64_t)ws_bytes < tail + 256) return 0;
     const size_t front = (size_t)(((int64_t)ws_bytes - tail) / 256 * 256);
-    if (front < step_f32_front(*tok, d, V, bwd_align(dtype))) return 0;
+    if (front < step_f32_min_front(*tok, d, V)) return 0;
     return bwd_tc_for(*tok, d, V, dtype, front);
   }
   return 0;
@@ -688,16 +704,19 @@ static rft_status loss_bwd(const rft_tokens* tok, const void* hidden, const void
   } else {
     const float* H = (const float*)hidden;
     const float* W = (const float*)weight;
+    const bool room = ws_bytes >= w.bytes + bwd_part_bytes(d, V, dtype, Tc);
+    float* const part = room ? (float*)((char*)ws + w.bytes) : nullptr;
     for (int64_t ci = 0; ci < nchunks; ++ci) {
       int64_t c0 = ci * Tc;
       RFT_HIP(f32_dz(H, d, W, V, w.Vpad, w.m.rows, tok->token_ids, lse, grad_logp, grad_entropy,
                      entropy, cnt, c0, Tc, w.dz32, s),
               fn);
-      // d_weight is overwritten by this chunk's dW: until then it is free for
-      // the partial sums of a dH whose few rows need K split
+      // where dH splits K and the workspace has no room for its partial sums, a
+      // d_weight that this chunk's dW overwrites is free for them until then;
+      // one that is added to is not, and dH takes the same slices in turn
       const bool fresh = ci == 0 && !accumulate_dw;
       RFT_HIP(f32_dh(w.dz32, w.Vpad, W, V, d, Tc, cnt, c0, w.m.rows, d_hidden,
-                     fresh ? d_weight : nullptr, fresh ? V * d : 0, s),
+                     part ? part : fresh ? d_weight : nullptr, s),
               fn);
       RFT_HIP(f32_dw(w.dz32, w.Vpad, H, d, V, Tc, cnt, c0, w.m.rows, d_weight, fresh ? 0 : 1, s),
               fn);
@@ -810,9 +829,9 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
   const float* ref = ref_logp;
   const bool bonus = params->entropy_coef > 0.f;
   if (dtype == RFT_F32) {
-    if ((st = check_ws(fn, ws, ws_bytes, step_f32_bytes(*tok, d, V, bwd_align(dtype))))) return st;
+    if ((st = check_ws(fn, ws, ws_bytes, step_f32_min_front(*tok, d, V) + step_f32_tail(*tok)))) return st;
     // the three calls share the front; the largest chunk that fits leaves room for egrad
-    int64_t front = (int64_t)ws_bytes - round_up((tok->T > 0 ? tok->T : 1) * 4, 256);
+    int64_t front = (int64_t)ws_bytes - (int64_t)step_f32_tail(*tok);
     front = front / 256 * 256;
     float* egrad = bonus ? (float*)((char*)ws + front) : nullptr;
     if ((st = rft_token_logprobs(tok, hidden, weight, dtype, d, V, logp, entropy, lse, ws,

@@ -420,8 +420,9 @@ hipError_t f32_dz(const float* H, int64_t d, const float* W, int64_t V, int64_t 
                   const float* egrad, const float* ent, const int32_t* cnt, int64_t c0,
                   int64_t Tc, float* dz, hipStream_t s);
 hipError_t f32_dh(const float* dz, int64_t Vpad, const float* W, int64_t V, int64_t d, int64_t Tc,
-                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* scratch,
-                  int64_t scratch_elems, hipStream_t s);
+                  const int32_t* cnt, int64_t c0, const int32_t* rows, float* dH, float* part,
+                  hipStream_t s);
+int64_t f32_dh_part_elems(int64_t Tc, int64_t d, int64_t V);
 hipError_t f32_dw(const float* dz, int64_t Vpad, const float* H, int64_t d, int64_t V, int64_t Tc,
                   const int32_t* cnt, int64_t c0, const int32_t* rows, float* dW, int accumulate,
                   hipStream_t s);
