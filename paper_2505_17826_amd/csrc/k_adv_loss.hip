@@ -687,7 +687,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_rows(
     int ntiles, int64_t ld, const float* __restrict__ zy, float* __restrict__ logp,
     float* __restrict__ ent, float* __restrict__ lse) {
   __shared__ RowStats sh[kMergeThreads];
-  const int64_t t = (int64_t)blockIdx.x * kMergeRows + threadIdx.x % kMergeRows;
+  const int64_t t = block_index() * kMergeRows + threadIdx.x % kMergeRows;
   const int k = t < T ? kidx[t] : -1;
   const RowStats r = merge_tiles(pm + (k < 0 ? 0 : k), ps + (k < 0 ? 0 : k), pu + (k < 0 ? 0 : k), ld,
                                ntiles, k >= 0, sh);
@@ -710,8 +710,8 @@ hipError_t launch_merge_rows(const rft_tokens& tok, const TokMeta& m, int64_t V,
                              const float* zy, float* logp, float* ent, float* lse, hipStream_t s) {
   const int64_t nb = (tok.T + kMergeRows - 1) / kMergeRows;
   if (nb > 0)
-    k_merge_rows<<<(unsigned)nb, kMergeThreads, 0, s>>>(m.kidx, tok.token_ids, tok.T, V, pm, ps, pu, ntiles, ld, zy,
-                                    logp, ent, lse);
+    k_merge_rows<<<grid_xy(nb), kMergeThreads, 0, s>>>(m.kidx, tok.token_ids, tok.T, V, pm, ps, pu,
+                                                       ntiles, ld, zy, logp, ent, lse);
   return hipGetLastError();
 }
 
