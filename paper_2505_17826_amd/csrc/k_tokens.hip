@@ -39,11 +39,13 @@ __device__ __forceinline__ int count_range(const uint8_t* __restrict__ mask, int
 // blocks: valid rows of each rollout.
 __global__ void __launch_bounds__(kThreads) k_count(const uint8_t* __restrict__ mask,
                                                     const int32_t* __restrict__ ss, int64_t T,
-                                                    int64_t nblk, int32_t* __restrict__ blk,
+                                                    int64_t nblk, int64_t n_seq,
+                                                    int32_t* __restrict__ blk,
                                                     int32_t* __restrict__ n_i,
                                                     int32_t* __restrict__ meta) {
   __shared__ int red[4];
-  const int64_t b = blockIdx.x;
+  const int64_t b = block_index();
+  if (b >= nblk + n_seq) return;
   int64_t lo, hi;
   if (b < nblk) {
     lo = b * kK0Rows;
@@ -153,8 +155,8 @@ hipError_t launch_tokmeta(const rft_tokens& tok, const TokMeta& m, hipStream_t s
   }
   const int64_t nblk = (T + kK0Rows - 1) / kK0Rows;
   if (nblk + n_seq > 0)
-    k_count<<<(unsigned)(nblk + n_seq), kThreads, 0, s>>>(tok.mask, tok.seq_start, T, nblk, m.blk,
-                                                          m.n_i, m.meta);
+    k_count<<<grid_xy(nblk + n_seq), kThreads, 0, s>>>(tok.mask, tok.seq_start, T, nblk, n_seq,
+                                                       m.blk, m.n_i, m.meta);
   if (nblk == 0 || nblk > kSelfBlocks)
     k_scan<<<1, kThreads, 0, s>>>(m.blk, (int)nblk, m.n_i, n_seq, tok.is_expert, m.meta);
   if (nblk > kSelfBlocks)

@@ -37,3 +37,25 @@ def test_token_logprobs_of_2_28_rows():
     for x in (logp, ent, lse):
         assert int(torch.count_nonzero(x)) <= rows.numel()
         assert int(torch.count_nonzero(x[5:(1 << 28) - 3])) == 0
+
+
+@pytest.mark.parametrize("n_seq", [(1 << 24) - 1])
+def test_bookkeeping_of_2_24_rollouts(n_seq):
+    """One workgroup per rollout beside those of the rows' blocks: almost all
+    rollouts empty, the last ones hold all the rows."""
+    T, last = 100000, 1000
+    print(f"[launch limits] n_seq={n_seq}", flush=True)
+    start = torch.zeros(n_seq + 1, dtype=torch.int32, device=DEV)
+    start[n_seq - last:] = torch.arange(last + 1, dtype=torch.int32, device=DEV) * (T // last)
+    g = torch.Generator().manual_seed(1)
+    mask = (torch.rand(T, generator=g) < 0.5).to(torch.uint8).to(DEV)
+    logp = -torch.rand(T, generator=g).to(DEV)
+    tok = R.Tokens(start, mask, torch.zeros(T, dtype=torch.int32, device=DEV))
+    grad, st = R.rft_sft_loss_fwd(tok, 10, logp, agg=R.RFT_AGG_SEQ_MEAN_TOKEN_MEAN)
+    n = mask.view(last, -1).double().sum(1)
+    w = (mask.view(last, -1).double() / (last * n[:, None])).view(-1)
+    s = R.stats_to_dict(st)
+    assert s["n_valid"] == int(mask.sum()) and s["n_seq_valid"] == last
+    # fp64 sums of T terms
+    assert math.isclose(s["loss"], float((w * -logp.double()).sum()), rel_tol=T * 2.0 ** -53)
+    assert (grad.double() + w).abs().max() <= 2.0 ** -24 * w.max()
