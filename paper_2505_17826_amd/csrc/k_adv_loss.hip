@@ -12,7 +12,7 @@ __global__ void __launch_bounds__(256) k_group_adv(const float* __restrict__ r, 
                                                    int G, float eps, int unbiased,
                                                    float* __restrict__ adv) {
   int lane = threadIdx.x & 63;
-  int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  int64_t g = block_index() * 4 + (threadIdx.x >> 6);
   if (g >= n_groups) return;
   const float* rg = r + g * G;
   double s = 0.0;
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) k_group_adv(const float* __restrict__ r, 
 hipError_t launch_group_adv(const float* r, int64_t n_groups, int G, float eps, int unbiased,
                             float* adv, hipStream_t s) {
   if (n_groups > 0)
-    k_group_adv<<<(unsigned)((n_groups + 3) / 4), 256, 0, s>>>(r, n_groups, G, eps, unbiased, adv);
+    k_group_adv<<<grid_xy((n_groups + 3) / 4), 256, 0, s>>>(r, n_groups, G, eps, unbiased, adv);
   return hipGetLastError();
 }
 
@@ -275,13 +275,14 @@ __global__ void __launch_bounds__(256) k_adv_few(const float* __restrict__ r,
 // LDS per workgroup.
 template <int LO, int CAP>
 __global__ void __launch_bounds__(256) k_adv_member_groups(
-    const float* __restrict__ r, const int32_t* __restrict__ gid, int64_t n,
+    const float* __restrict__ r, const int32_t* __restrict__ gid, int64_t n, int64_t n_groups,
     const int32_t* __restrict__ off, const int32_t* __restrict__ mem, int mode, float eps,
     int unbiased, float* __restrict__ adv) {
   __shared__ int32_t key[CAP];
   __shared__ double shd[4];
   __shared__ float shf[4];
-  const int g = (int)blockIdx.x;
+  if (block_index() >= n_groups) return;
+  const int g = (int)block_index();
   const int64_t a0 = off[g];
   const int G = off[g + 1] - (int32_t)a0;
   if (G <= LO || (CAP < kAdvSortCap && G > CAP)) return;
@@ -387,10 +388,10 @@ hipError_t launch_group_adv_ids(const float* r, const int32_t* gid, int64_t n, i
   k_adv_scan_top<<<1, 256, 0, s>>>(w.tot, nbs);
   k_adv_scan_apply<<<(unsigned)nbs, 256, 0, s>>>(w.cnt, n_groups, w.tot, w.off);
   k_adv_scatter<<<nbn, 256, 0, s>>>(gid, n, n_groups, w.off, w.cur, w.mem);
-  k_adv_member_groups<0, kAdvSortSmall><<<(unsigned)n_groups, 256, 0, s>>>(
-      r, gid, n, w.off, w.mem, mode, eps, unbiased, adv);
-  k_adv_member_groups<kAdvSortSmall, kAdvSortCap><<<(unsigned)n_groups, 256, 0, s>>>(
-      r, gid, n, w.off, w.mem, mode, eps, unbiased, adv);
+  k_adv_member_groups<0, kAdvSortSmall><<<grid_xy(n_groups), 256, 0, s>>>(
+      r, gid, n, n_groups, w.off, w.mem, mode, eps, unbiased, adv);
+  k_adv_member_groups<kAdvSortSmall, kAdvSortCap><<<grid_xy(n_groups), 256, 0, s>>>(
+      r, gid, n, n_groups, w.off, w.mem, mode, eps, unbiased, adv);
   return hipGetLastError();
 }
 

@@ -16,6 +16,8 @@
 // V and the base need no alignment.  Every kernel here gives each thread the
 // same chunks of the row in the same order, so the statistics-only,
 // d_logits-only and fused kernels agree bit for bit.
+#include <algorithm>
+
 #include "rft_internal.h"
 #include "tokens_device.h"
 
@@ -522,11 +524,23 @@ __global__ void __launch_bounds__(NTC, WPS) k_logits_fused_cached(
 
 }  // namespace lg
 
+// Rows per launch: one workgroup of 512 threads per row, and a launch holds fewer
+// than 2^32 work-items in x.  (The row's index from y as well, in one launch,
+// cost the one-workgroup variant 2.4%.)
+constexpr int64_t kLaunchRows = (int64_t)1 << 22;
+template <class T>
+static T* from(T* p, int64_t i) {
+  return p ? p + i : nullptr;
+}
+
 hipError_t launch_logits_stats(const float* logits, const rft_tokens& tok, int64_t V, float* logp,
                                float* ent, float* lse, float* gathered, hipStream_t s) {
-  if (tok.T <= 0) return hipSuccess;
-  lg::k_logits_stats<<<(unsigned)tok.T, lg::NT, 0, s>>>(logits, tok.T, V, tok.mask, tok.token_ids,
-                                                        logp, ent, lse, gathered);
+  for (int64_t t0 = 0; t0 < tok.T; t0 += kLaunchRows) {
+    const int64_t n = std::min(tok.T - t0, kLaunchRows);
+    lg::k_logits_stats<<<(unsigned)n, lg::NT, 0, s>>>(logits + t0 * V, n, V, tok.mask + t0,
+                                                      tok.token_ids + t0, logp + t0, from(ent, t0),
+                                                      lse + t0, from(gathered, t0));
+  }
   return hipGetLastError();
 }
 
@@ -551,8 +565,12 @@ hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t
   hipError_t e = row_parts(tok.T, V, &lp);
   if (e != hipSuccess) return e;
   auto k = egrad ? lg::k_logits_bwd<true> : lg::k_logits_bwd<false>;
-  k<<<(unsigned)(tok.T << lp), lg::NT >> lp, 0, s>>>(logits, V, tok.mask, tok.token_ids, lse, grad,
-                                                     egrad, ent, dl, lp);
+  for (int64_t t0 = 0; t0 < tok.T; t0 += kLaunchRows) {
+    const int64_t n = std::min(tok.T - t0, kLaunchRows);
+    k<<<(unsigned)(n << lp), lg::NT >> lp, 0, s>>>(logits + t0 * V, V, tok.mask + t0,
+                                                   tok.token_ids + t0, lse + t0, grad + t0,
+                                                   from(egrad, t0), from(ent, t0), dl + t0 * V, lp);
+  }
   return hipGetLastError();
 }
 
@@ -613,25 +631,25 @@ hipError_t launch_logits_fused(const float* logits, const rft_tokens& tok, const
     return launch_logits_bwd(logits, tok, V, terms, terms + tok.T, bonus ? terms + 2 * tok.T : nullptr,
                              bonus ? terms + 3 * tok.T : nullptr, dl, s);
   }
-  if (tok.T > 0) {
-    // buffer descriptors span one row: 32-bit byte offsets
-    if (V > ((int64_t)1 << 28)) {
-      lg::k_logits_fused<<<(unsigned)tok.T, lg::NT, 0, s>>>(
-          logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i, m.meta, old, ref,
-          adv, c, logp, ent, lse, grad, dl, parts);
-      e = hipGetLastError();
+  const bool al = V % 4 == 0 && (((uintptr_t)logits | (uintptr_t)dl) & 15) == 0;
+  for (int64_t t0 = 0; t0 < tok.T && e == hipSuccess; t0 += kLaunchRows) {
+    const int64_t n = std::min(tok.T - t0, kLaunchRows);
+    auto go = [&](auto k) {
+      return k(logits + t0 * V, n, V, tok.mask + t0, tok.token_ids + t0, m.kidx + t0, m.row_seq,
+               m.n_i, m.meta, old + t0, from(ref, t0), adv, c, logp + t0, from(ent, t0),
+               from(lse, t0), from(grad, t0), dl + t0 * V, parts + t0);
+    };
+    if (V > ((int64_t)1 << 28)) {  // buffer descriptors span one row: 32-bit byte offsets
+      e = go([&](auto... a) {
+        lg::k_logits_fused<<<(unsigned)n, lg::NT, 0, s>>>(a...);
+        return hipGetLastError();
+      });
+    } else if (c.ent_coef > 0.f) {
+      e = al ? go([&](auto... a) { return fused_any<true, true>(V, n, s, a...); })
+             : go([&](auto... a) { return fused_any<true, false>(V, n, s, a...); });
     } else {
-      const bool al = V % 4 == 0 && (((uintptr_t)logits | (uintptr_t)dl) & 15) == 0;
-      auto go = [&](auto k) {
-        return k(V, tok.T, s, logits, tok.T, V, tok.mask, tok.token_ids, m.kidx, m.row_seq, m.n_i,
-                 m.meta, old, ref, adv, c, logp, ent, lse, grad, dl, parts);
-      };
-      if (c.ent_coef > 0.f)
-        e = al ? go([](auto... a) { return fused_any<true, true>(a...); })
-               : go([](auto... a) { return fused_any<true, false>(a...); });
-      else
-        e = al ? go([](auto... a) { return fused_any<false, true>(a...); })
-               : go([](auto... a) { return fused_any<false, false>(a...); });
+      e = al ? go([&](auto... a) { return fused_any<false, true>(V, n, s, a...); })
+             : go([&](auto... a) { return fused_any<false, false>(V, n, s, a...); });
     }
   }
   if (e != hipSuccess) return e;

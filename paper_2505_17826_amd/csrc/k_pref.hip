@@ -31,12 +31,14 @@ __device__ Tv block_sum(Tv v, Tv* sh) {
 
 __global__ void __launch_bounds__(kPrefT) k_dpo_seq(
     const int32_t* __restrict__ seq_start, const uint8_t* __restrict__ mask,
-    const int32_t* __restrict__ ids, int64_t T, int64_t V, const float* __restrict__ logp,
+    const int32_t* __restrict__ ids, int64_t T, int64_t n_seq, int64_t V,
+    const float* __restrict__ logp,
     const float* __restrict__ ref, double* __restrict__ pi, double* __restrict__ rho,
     int32_t* __restrict__ bad, float* __restrict__ seq_logp) {
   __shared__ double shd[kPrefT / 64];
   __shared__ int shi[kPrefT / 64];
-  const int64_t s = blockIdx.x;
+  const int64_t s = block_index();
+  if (s >= n_seq) return;
   int64_t a = seq_start[s], b = seq_start[s + 1];
   a = a < 0 ? 0 : (a > T ? T : a);
   b = b < a ? a : (b > T ? T : b);
@@ -143,9 +145,9 @@ hipError_t launch_dpo(const rft_tokens& tok, const TokMeta& m, int64_t V, const 
                       const float* ref, float beta, float ls, const DpoWs& w, float* grad,
                       float* seq_logp, rft_dpo_stats* st, hipStream_t s) {
   if (tok.n_seq > 0)
-    k_dpo_seq<<<(unsigned)tok.n_seq, kPrefT, 0, s>>>(tok.seq_start, tok.mask, tok.token_ids,
-                                                     tok.T, V, logp, ref, w.pi, w.rho, w.bad,
-                                                     seq_logp);
+    k_dpo_seq<<<grid_xy(tok.n_seq), kPrefT, 0, s>>>(tok.seq_start, tok.mask, tok.token_ids, tok.T,
+                                                    tok.n_seq, V, logp, ref, w.pi, w.rho, w.bad,
+                                                    seq_logp);
   // one wave for few pairs: its block sums cost a barrier and an LDS round each
   k_dpo_pairs<<<1, tok.n_seq <= 512 ? 64 : 1024, 0, s>>>(tok.n_seq / 2, m.n_i, m.meta, w.pi, w.rho, w.bad, (double)beta,
                                  (double)ls, w.coef, st);

@@ -225,13 +225,14 @@ struct Carver {
 constexpr int kK0Rows = 2048;  // rows per block of the compaction kernels
 
 // A launch holds fewer than 2^32 work-items in x: grids of nb blocks that may
-// pass it continue in y (block_index; blocks past nb must return).
+// pass it go on in y after each 2^20 (block_index; blocks past nb must return).
+constexpr int kGridX = 20;
 inline dim3 grid_xy(int64_t nb) {
-  const int64_t bx = nb < (1 << 20) ? nb : (1 << 20);
-  return dim3((unsigned)bx, (unsigned)((nb + bx - 1) / bx));
+  const int64_t bx = (int64_t)1 << kGridX;
+  return nb <= bx ? dim3((unsigned)nb) : dim3((unsigned)bx, (unsigned)((nb + bx - 1) >> kGridX));
 }
 __device__ __forceinline__ int64_t block_index() {
-  return (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  return ((int64_t)blockIdx.y << kGridX) + blockIdx.x;
 }
 
 TokMeta carve_tokmeta(Carver& c, int64_t T, int64_t n_seq);
