@@ -170,7 +170,7 @@ __device__ __forceinline__ RowStats merge_tiles(const float* __restrict__ pm,
         const int64_t o = (int64_t)min(j + q, j1 - 1) * ld;
         a[q] = pm[o];
         b[q] = j + q < j1 ? ps[o] : 0.f;
-        c[q] = pu[o];
+        c[q] = j + q < j1 ? pu[o] : 0.f;  // not 0 times an infinite sum
       }
       float M = r.m;
 #pragma unroll
