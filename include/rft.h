@@ -257,7 +257,8 @@ rft_status rft_token_logprobs(const rft_tokens* tok, const void* hidden, const v
  * the actor's entropy).  This is the statistics half of the loss-only path,
  * for callers whose logits already exist.  gathered (may be NULL)
  * receives logits[t, id_t] (bit-exact copy; NaN for an out-of-range id).
- * Logits of -inf mark vocabulary entries the caller excludes: they get p = 0
+ * Logits of -inf (or of the type's lowest value, and all below -2e38) mark
+ * vocabulary entries the caller excludes: they get p = 0
  * and add 0 to the entropy, so the results are those of the vocabulary without
  * them (a row needs one finite logit).  The same holds in the loss-only and
  * d_logits calls, whose d_logits are exactly 0 in those columns. */

@@ -53,9 +53,11 @@ struct RowView {
 
 // Online (max, sum exp, sum exp * z) over a thread's logits.  Every exponent
 // argument is <= 0 (hardware exp2; results below 2^-126 flush to 0).  Logits
-// of -inf (masked entries) add nothing: while the running max is still -inf
-// the exponents are taken against 0, and z is clamped to the finite range in
-// the product exp * z (0 * z stays 0).
+// of -inf (masked entries) add nothing: while the running max is still below
+// kLowest the exponents are taken against 0, and z is clamped to the finite range
+// in the product exp * z (0 * z stays 0).  The same holds for entries masked by
+// the type's lowest value, whose product with log2(e) would overflow.
+constexpr float kLowest = -2e38f;  // 2e38 log2(e) is finite
 __device__ __forceinline__ float zfin(float z) { return fmaxf(z, -FLT_MAX); }
 
 __device__ __forceinline__ void acc4(RowStats& r, float4 q) {
@@ -66,7 +68,7 @@ __device__ __forceinline__ void acc4(RowStats& r, float4 q) {
     r.u *= sc;
     r.m = mq;
   }
-  float mk = r.m == -INFINITY ? 0.f : r.m * kLog2e;
+  float mk = r.m < kLowest ? 0.f : r.m * kLog2e;
   float e0 = __builtin_amdgcn_exp2f(fmaf(q.x, kLog2e, -mk));
   float e1 = __builtin_amdgcn_exp2f(fmaf(q.y, kLog2e, -mk));
   float e2 = __builtin_amdgcn_exp2f(fmaf(q.z, kLog2e, -mk));
@@ -82,7 +84,7 @@ __device__ __forceinline__ void acc1(RowStats& r, float z) {
     r.u *= sc;
     r.m = z;
   }
-  float e = __builtin_amdgcn_exp2f(fmaf(z, kLog2e, r.m == -INFINITY ? 0.f : -r.m * kLog2e));
+  float e = __builtin_amdgcn_exp2f(fmaf(z, kLog2e, r.m < kLowest ? 0.f : -r.m * kLog2e));
   r.s += e;
   r.u += e * zfin(z);
 }
