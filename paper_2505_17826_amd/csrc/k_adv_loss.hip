@@ -214,8 +214,8 @@ __global__ void __launch_bounds__(256) k_adv_few(const float* __restrict__ r,
                                                  const int32_t* __restrict__ gid, int n,
                                                  int64_t n_groups, int mode, float eps,
                                                  int unbiased, float* __restrict__ adv) {
-  __shared__ int sg[kAdvFew];
-  __shared__ float sr[kAdvFew];
+  __shared__ __align__(16) int sg[kAdvFew];  // read four at a time
+  __shared__ __align__(16) float sr[kAdvFew];
   const int n4 = (n + 3) & ~3;
   for (int j = threadIdx.x; j < n4; j += 256) {
     const int g = j < n ? gid[j] : -1;
