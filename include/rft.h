@@ -241,7 +241,7 @@ rft_status rft_group_advantages_ids(const float* rewards, const int32_t* group_i
  * recommended size; for bf16 with d % 64 == 0 it includes tile-blocked copies
  * of the valid hidden rows and of weight (about Vpad d 2 bytes more, Vpad = V
  * rounded up to 256), with which the GEMM of more than 10240 rows runs on
- * larger tiles.  Any size >=
+ * larger tiles (up to there they are not made, and the minimum is as fast).  Any size >=
  * rft_workspace_min_bytes() works and gives the same results bit for bit.
  * Outputs (f32, [T]): logp (NaN for a valid row whose id is out of range),
  * entropy (may be NULL), lse.  Masked rows are 0.  hidden and the outputs may

@@ -283,7 +283,8 @@ int64_t bwd_tc_for(const rft_tokens& tok, int64_t d, int64_t V, int dtype, size_
 // k-step of the backward GEMMs reads contiguous 32 KiB blocks.
 struct StepWs {
   TokMeta m;
-  uint16_t *hc, *wb, *wt, *dz, *dzt, *hct;  // hc [Tpad, Kp], wb [Vpad, Kp] blocked (forward)
+  uint16_t *hc, *wb, *wt, *dz, *dzt, *hct;  // hc [Tpad, Kp] blocked; wb [Vpad, Kp] too, or
+                                            //   nullptr (the forward reads the caller's W)
   float *pm, *ps, *pu, *zy;
   float *ce, *cmu;  // per chunk row: entropy-bonus coefficient and softmax mean
   LossPartial* parts;
@@ -302,7 +303,7 @@ StepWs carve_step(void* base, const rft_tokens& tok, int64_t d, int64_t V, int64
   w.dpad = round_up(d, kBf16Align);
   w.Kp = round_up(d, 64);
   w.hc = c.take<uint16_t>((size_t)round_up(T1, kBf16Align) * w.Kp);
-  w.wb = c.take<uint16_t>((size_t)w.Vpad * w.Kp);
+  w.wb = tok.T > kBlockedWRows ? c.take<uint16_t>((size_t)w.Vpad * w.Kp) : nullptr;
   w.wt = c.take<uint16_t>((size_t)w.dpad * w.Vpad);
   w.pm = c.take<float>((size_t)w.ntiles * Tc);
   w.ps = c.take<float>((size_t)w.ntiles * Tc);
@@ -857,7 +858,7 @@ rft_status rft_ppo_clip_step(const rft_tokens* tok, const void* hidden, const vo
   const uint16_t* W = (const uint16_t*)weight;
   const int64_t nchunks = T > 0 ? (T + Tc - 1) / Tc : 0;
   const int32_t* cnt = w.m.meta;
-  const bool blockedW = T > kBlockedWRows;
+  const bool blockedW = w.wb != nullptr;
   RFT_HIP(launch_tokmeta(*tok, w.m, s), fn);
   if (T > 0) {
     // masked rows of d_hidden and of the per-token outputs are 0; the chunks
