@@ -179,12 +179,13 @@ def _mask_vocab(logits, ids, mask, seed):
     return torch.from_numpy(z)
 
 
-@pytest.mark.parametrize("V,group", [(8192, 8), (8190, 8), (160000, 2)])
+@pytest.mark.parametrize("V,group", [(8192, 8), (8190, 8), (160000, 2), (160000, 9)])
 def test_masked_vocabulary_logits(V, group):
     """Loss-only paths on logits with -inf entries (reading R15): fused and
     separate calls against the oracle, no NaN anywhere, and d_logits exactly
-    0 in the masked columns.  V = 8190 takes the scalar path, V = 160000
-    exceeds the on-chip row cache."""
+    0 in the masked columns.  V = 8190: rows that start off the 16-byte
+    boundaries; V = 160000: 32 rows cut into parts, and 144 rows of one workgroup
+    each, which exceed the on-chip row cache."""
     cfg = synth.config(4, n_prompts=1, group=group, V=V)
     b = synth.make_batch(cfg, "cpu", seed_key=(4, 151, V))
     zm = _mask_vocab(b.logits, b.ids.numpy(), b.mask.numpy(), V)

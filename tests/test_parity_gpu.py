@@ -182,7 +182,8 @@ def test_loss_ratio_one_is_minus_mean_advantage():
 # V = 8192: every thread's row chunks fit in registers (ragged across threads);
 # 134692: the part kept in LDS ends mid-way; 152004: the LDS part ends just
 # before its capacity (rows up to 153600 stay on chip); 160004: a ragged
-# remainder past registers and LDS is read twice; 4099 and 1: scalar path.
+# remainder past registers and LDS is read twice; 4099 and 1: rows that start off
+# the 16-byte boundaries, and rows without a whole chunk of four.
 @pytest.mark.parametrize("V,n_prompts", [(8192, 16), (4099, 16), (1, 16), (134692, 2),
                                          (152004, 2), (160004, 2)])
 def test_logits_paths(V, n_prompts):
@@ -242,15 +243,21 @@ def test_logits_paths(V, n_prompts):
 # --------------------------------------------------------------- edge cases --
 @pytest.mark.parametrize("d,V,n_prompts", [(128, 2048, 4), (192, 5003, 6), (64, 300, 1)])
 def test_token_logprobs_blocked_equals_row_major(d, V, n_prompts):
-    """rft_token_logprobs with the recommended workspace (tile-blocked copies,
-    384 x 256 GEMM tiles) and with the minimum workspace (row-major operands,
-    256 x 256 tiles): the same numbers bit for bit, and the oracle's."""
+    """rft_token_logprobs of more than 10240 rows (masked rows after the batch's) with
+    the recommended workspace (tile-blocked copies, 384 x 256 GEMM tiles) and with
+    the minimum workspace (row-major operands, 256 x 256 tiles): the same numbers
+    bit for bit, and the oracle's."""
     over = dict(n_prompts=n_prompts, group=8, len_lo=1, len_hi=200, pad_to=200, d=d, V=V,
                 dtype="bf16")
     b = _batch(1, f"blk{d}-{V}", over)
-    print(f"[fwd blocked] d={d} V={V} T={b.T} N={int(b.mask.sum())}", flush=True)
-    tok = tokens_of(b)
-    H, W = b.H.to(DEV).contiguous(), b.W.to(DEV).contiguous()
+    T, extra = b.T, 10241 + 300 - b.T
+    assert extra > 0
+    print(f"[fwd blocked] d={d} V={V} T={T} + {extra} N={int(b.mask.sum())}", flush=True)
+    start = b.seq_start.clone()
+    start[-1] += extra
+    more = lambda x, v: torch.cat([x, torch.full((extra, *x.shape[1:]), v, dtype=x.dtype)])  # noqa: E731
+    tok = R.Tokens(start.to(DEV), more(b.mask, 0).to(DEV), more(b.ids, 0).to(DEV))
+    H, W = more(b.H, float("nan")).to(DEV), b.W.to(DEV).contiguous()
     big = R.workspace_bytes(R.RFT_OP_TOKEN_LOGPROBS, tok, d, V, R.RFT_BF16)
     small = R.workspace_bytes(R.RFT_OP_TOKEN_LOGPROBS, tok, d, V, R.RFT_BF16, minimum=True)
     assert big > small
@@ -261,10 +268,11 @@ def test_token_logprobs_blocked_equals_row_major(d, V, n_prompts):
     torch.cuda.synchronize()
     for a_, b_, k in zip(outs[0], outs[1], ("logp", "entropy", "lse")):
         assert np.array_equal(a_, b_), (k, np.nanmax(np.abs(a_ - b_)))
+        assert np.all(a_[T:] == 0)
     m = b.mask.numpy() != 0
     for got, want, k in zip(outs[0], O.token_logprobs(b.H, b.W, b.ids, b.mask),
                             ("logp", "entropy", "lse")):
-        assert np.abs(got[m] - np.asarray(want)[m]).max() <= TOL_LOGP, k
+        assert np.abs(got[:T][m] - np.asarray(want)[m]).max() <= TOL_LOGP, k
 
 
 def test_all_masked_batch():
