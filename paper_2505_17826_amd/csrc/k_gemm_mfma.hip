@@ -4,7 +4,8 @@
 // wave's LDS and barrier waits overlap the other's MFMAs), each owning 64x128
 // of C as 4x8 v_mfma_f32_16x16x32_bf16 tiles (fp32 accumulators).  Operands go
 // straight from HBM/L2 into LDS with buffer_load_dwordx4 ... lds (no staging
-// registers), issued by four of the eight waves; the buffer descriptor covers only the tile's valid rows, so rows
+// registers), issued by two or four of the eight waves (kNLoad; by all of them in
+// k_gemm384); the buffer descriptor covers only the tile's valid rows, so rows
 // past the end and the K tail read as zeros without branches.  LDS holds
 // 16-byte chunks XOR-swizzled by row pair (conflict-free ds_read_b128 of MFMA
 // fragments in the 64-bank LDS) in two stages.  Workgroups map to tiles so
@@ -232,7 +233,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int64
 // read from outside the descriptor (0).
 // Loader waves per epilogue: two for the GEMMs on tile-blocked operands (dH
 // and dW: 1-1.7% faster than four; the fused step's forward: 3% faster than
-// four, one 15% slower), four for the forward on row-major operands.
+// four, one 15% slower), four for the forward on row-major operands.  The step's
+// forward also reads a row-major W (blocked rows, up to 10240 of them): two and
+// four waves take the same time there (steps of 1024, 2048, 4096 and 8192 rows at
+// d = 3584: 3.78, 6.51, 12.0, 22.9 ms with either).
 template <int EPI> constexpr int kNLoad = (EPI == EPI_STORE || EPI == EPI_STATS_Y) ? 2 : 4;
 struct LoadGeom {
   uint32_t vA[2], vB[2];  // per-lane byte offsets for even / odd p (k0 = 0)

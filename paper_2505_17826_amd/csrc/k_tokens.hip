@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(kThreads) k_count(const uint8_t* __restrict__ 
 
 // S, expert tokens and expert rollouts with tokens (all threads of one block).
 __device__ void seq_totals(const int32_t* __restrict__ n_i, int64_t n_seq,
-                           const uint8_t* __restrict__ is_expert, int N, int* red,
+                           const uint8_t* __restrict__ is_expert, int N,
                            int32_t* __restrict__ meta) {
   int s = 0, ne = 0, se = 0;
   for (int64_t i = threadIdx.x; i < n_seq; i += kThreads) {
@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(kThreads) k_scan(int32_t* __restrict__ blk, in
     if (b < nblk) blk[b] = carry + ex;
     carry += total;
   }
-  seq_totals(n_i, n_seq, is_expert, carry, red, meta);
+  seq_totals(n_i, n_seq, is_expert, carry, meta);
 }
 
 // The rollouts' starts go to LDS where they fit: the search for a row's rollout
@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(kThreads) k_scatter(const rft_tokens tok, TokM
     for (int b = threadIdx.x; b < (int)blockIdx.x; b += kThreads) v += m.blk[b];
     base = block_sum_int(v, red);
     if ((int)blockIdx.x == nblk - 1)  // base + its own count = N
-      seq_totals(m.n_i, tok.n_seq, tok.is_expert, base + m.blk[blockIdx.x], red, m.meta);
+      seq_totals(m.n_i, tok.n_seq, tok.is_expert, base + m.blk[blockIdx.x], m.meta);
   }
   int total;
   const int off = base + block_excl_scan(__builtin_popcount(f), red, &total);

@@ -140,11 +140,16 @@ struct FwdWs {
   size_t bytes;
 };
 bool fwd_blocked_ok(int dtype, int64_t d) { return dtype == RFT_BF16 && mfma_fwd_blk_ok(d); }
-// Whether the forward GEMM of T rows reads a tile-blocked copy of W: the copy
-// (440 us at d = 3584, V = 152064) is worth its cost from about 6600 valid rows
-// on, where the blocked operand and the 384-row tile save as much (6% of the
-// GEMM); both sides scale with V d.  T stands for the rows, of which about 60%
-// are valid in a padded batch.  The results are the same bit for bit.
+// Whether the forward GEMM of T rows reads a tile-blocked copy of W on the 384-row
+// tile (the copy takes 440 us at d = 3584, V = 152064), or the caller's row-major W
+// on the 256-row one.  By valid rows, row-major against copy (ms): the forward at
+// d = 3584, V = 152064 3.52 / 3.76 at 4096, 6.69 / 6.98 at 8192, 8.25 / 8.59 at
+// 10240, 16.0 / 16.4 at 20480, 22.4 / 21.5 at 28672; at d = 1536 3.17 / 3.20 at 8192,
+// 7.57 / 7.57 at 20480, 10.4 / 9.7 at 28672; the whole step at d = 3584 22.5 / 22.9 at
+// 8192, 27.4 / 27.4 at 10240, 37.5 / 37.3 at 14336, 74.3 / 73.3 at 28672, at d = 1536
+// 10.9 / 11.1 at 8192 and 37.7 / 37.0 at 28672.  So up to 10240 rows, valid or not, row-major is the
+// faster one; from there to about 20000 valid rows both are within 3%, and above
+// the copy is.  The results are the same bit for bit.
 constexpr int64_t kBlockedWRows = 10240;
 // blocked: the bf16 forward from tile-blocked copies of the compacted rows
 // [round_up(T, 256), d] and of W [Vpad, d] (d a multiple of 64), for the
