@@ -39,14 +39,14 @@ WORKLOADS = {"tiny": 0, "1.5b": 1, "7b": 2, "longcot": 3, "lossonly": 4}
 TRAFFIC = {
     # forward GEMM alone (k_gemm384<EPI_STATS> on the tile-blocked copies, one launch over
     # all valid rows)
-    "7b": {"sources": {'k_gemm_mfma.hip': '90fcec7603bc95eb', 'rft_internal.h': 'eba41893a97440c2'},
-           "bytes": 174218929.2 * 1024 * 2.0 + 1174427.7 * 1024 * 1.0},
+    "7b": {"sources": {'k_gemm_mfma.hip': '0cc59ef48596356f', 'rft_internal.h': 'a778fbc47a9f52d0'},
+           "bytes": 171001716.1 * 1024 * 2.0 + 1174431.1 * 1024 * 1.0},
     # every kernel of one rft_ppo_clip_step call and its advantages (24 dispatches, two
     # row chunks)
-    "step_7b": {"sources": {'k_gemm_mfma.hip': '90fcec7603bc95eb', 'k_step.hip': 'a920d8a6385f4246', 'k_layout.hip': '59fafc69e9c8b096', 'k_adv_loss.hip': '645923f87d774313', 'k_tokens.hip': '45fb1d5641296ae5', 'tokens_device.h': '73eabd5a3070690d', 'rft_internal.h': 'eba41893a97440c2', 'rft_abi.hip': '4945fc524dee1e45'},
-                "bytes": 623616757.6 * 1024 * 2.0 + 164163235.7 * 1024 * 1.0},
-    "lossonly": {"sources": {'k_logits.hip': 'a5f96d785b04e5ec', 'rft_internal.h': 'eba41893a97440c2'},
-                 "bytes": 8759825.4 * 1024 * 2.0 + 19500315.8 * 1024 * 1.0},
+    "step_7b": {"sources": {'k_gemm_mfma.hip': '0cc59ef48596356f', 'k_step.hip': 'a920d8a6385f4246', 'k_layout.hip': '59fafc69e9c8b096', 'k_adv_loss.hip': '3e2b860017848fdf', 'k_tokens.hip': '2e004762720e0e21', 'tokens_device.h': '73eabd5a3070690d', 'rft_internal.h': 'a778fbc47a9f52d0', 'rft_abi.hip': '0a71af3bbc7c6fe8'},
+                "bytes": 625386268.1 * 1024 * 2.0 + 164161177.3 * 1024 * 1.0},
+    "lossonly": {"sources": {'k_logits.hip': '4e0ce80d9e03b5ba', 'rft_internal.h': 'a778fbc47a9f52d0'},
+                 "bytes": 8758802.7 * 1024 * 2.0 + 19480270.7 * 1024 * 1.0},
 }
 
 

@@ -18,8 +18,9 @@
 // flight during the products; one barrier per step), and the fragments of
 // four K are read while the previous four's products run.  Measured (one pass
 // of forward, recompute, dH and dW; 1527 of 2048 rows valid, d = 1024, V =
-// 32000): 13.7 ms with the 64 x 64 vector-FMA tiles this replaces, 3.50 ms now;
-// the products run at 100-120 TFLOP/s, the matrix pipe 60-82% busy at 2.2 GHz
+// 32000): 13.7-14.6 ms with the 64 x 64 vector-FMA tiles this replaces, 3.5-3.8 ms
+// now on the same cards; the products run at 95-110 TFLOP/s, the matrix pipe 60-68%
+// busy at 2.2-2.4 GHz
 // (rocBLAS's largest fp32 product on the same card: 153).  Eight waves of 32 x 64
 // per tile and a wave priority by workgroup changed nothing.
 //

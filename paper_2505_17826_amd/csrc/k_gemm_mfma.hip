@@ -803,11 +803,13 @@ __global__ void __launch_bounds__(NT, 1) k_gemm(const Args g) {
 // priority.  A step has four such phases per wave; its share of the next stage's
 // loads goes out in the first two, once every wave has passed the barrier after
 // its last reads of that buffer, and is waited for in the last one, before the
-// barrier that precedes the first read.  The matrix pipe is busy 81% of the
-// cycles in d_weight (42000 rows, d = 3584, V = 152064), 72% with two loader waves
-// and one barrier per step; the card's power limit lowers the clock from 1.75 to
-// 1.65 GHz, so 35.3 -> 33.4 ms remain (1.38 PFLOP/s), and 1% of the forward.  The
-// same schedule with two phases of 32 made the 256 x 256 tile 5% slower.
+// barrier that precedes the first read.  The matrix pipe is busy 78-79% of the
+// cycles in d_weight and 79-81% in d_hidden (42000 and 131072 rows, d = 3584, V =
+// 152064), 78% in the forward alone, 74% with the y store; 67-74% with two loader
+// waves and one barrier per step.  The card's power limit holds the clock at 1.72-1.79
+// GHz there, so d_weight of 42000 rows went 35.3 -> 32.4-33.4 ms (1.38-1.45 PFLOP/s),
+// and the forward gained 1%.  The same schedule with two phases of 32 made the
+// 256 x 256 tile 5% slower.
 constexpr int BM4 = 384;
 constexpr int A_BYTES4 = BM4 * BK * 2;      // 48 KiB
 constexpr int STAGE4 = A_BYTES4 + B_BYTES;  // 80 KiB
