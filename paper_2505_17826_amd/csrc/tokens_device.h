@@ -73,16 +73,21 @@ __device__ __forceinline__ uint32_t mask8(const uint8_t* __restrict__ mask, int6
 // The rows and rollout of the flagged rows t0 .. t0 + 7 from compacted index
 // off on; ss is seq_start (LDS or global).  The rollout of a row is the largest
 // i in [0, n_seq) with ss[i] <= t, searched for the first row and walked from
-// there (always in bounds).
+// there, or searched again where more than four rollouts lie between two rows
+// (empty ones: walking 30000 of them took 2.2 ms; always in bounds).
 template <typename P>
 __device__ __forceinline__ void place8(uint32_t f, int64_t t0, int64_t T, P ss, int n_seq, int off,
                                        int32_t* __restrict__ rows, int32_t* __restrict__ row_seq,
                                        int32_t* __restrict__ kidx) {
-  int lo = 0, hi = n_seq - 1;
-  while (f && lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if ((int64_t)ss[mid] <= t0) lo = mid; else hi = mid - 1;
-  }
+  int lo = 0;
+  auto search = [&](int64_t t) {
+    int hi = n_seq - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if ((int64_t)ss[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+  };
+  if (f) search(t0);
   int64_t next = lo + 1 < n_seq ? (int64_t)ss[lo + 1] : T;  // first row of the next rollout
   int kx[8];
 #pragma unroll
@@ -90,8 +95,8 @@ __device__ __forceinline__ void place8(uint32_t f, int64_t t0, int64_t T, P ss, 
     const int64_t t = t0 + j;
     kx[j] = -1;
     if (f >> j & 1) {
-      while (next <= t) {
-        ++lo;
+      for (int w = 0; next <= t; ++w) {
+        if (w < 4) ++lo; else search(t);
         next = lo + 1 < n_seq ? (int64_t)ss[lo + 1] : T;
       }
       rows[off] = (int32_t)t;
