@@ -157,9 +157,10 @@ __device__ __forceinline__ float dlogit1(float z, float lk, float c, float e, fl
   return ENT ? dlogit(c, e, mu, p, z, hot) : c * ((hot ? 1.f : 0.f) - p);
 }
 
-// d_logits of one row: c (onehot - p) + e p (z - mu), 16-byte stores; vt: the
-// thread's place among the row's NT threads.
-template <bool ENT>
+// d_logits of one row: c (onehot - p) + e p (z - mu), 16-byte stores, by ST
+// threads; vt: the thread's place among them.  UN chunks' loads in flight at a
+// time; with one wavefront per row also of a lane's last few chunks.
+template <bool ENT, int UN, int ST = NT>
 __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, float c, float e,
                           float mu, int y, float* __restrict__ out, int vt) {
   const float lk = lse * kLog2e;
@@ -167,20 +168,31 @@ __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, flo
   const floatx4* z4 = (const floatx4*)rv.z4;
   float* const o4 = out + rv.h;
   const int yc = y - rv.h;
-  // eight chunks' loads in flight at a time
-  constexpr int UN = 8;
   int64_t j = vt;
-  for (; j + (UN - 1) * NT < rv.n4; j += UN * NT) {
+  for (; j + (UN - 1) * ST < rv.n4; j += UN * ST) {
     floatx4 q[UN];
 #pragma unroll
-    for (int u = 0; u < UN; ++u) q[u] = z4[j + u * NT];
+    for (int u = 0; u < UN; ++u) q[u] = z4[j + u * ST];
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      __builtin_nontemporal_store((f4u)dlogit4<ENT>(q[u], lk, c, e, mu, j + u * NT, yc),
-                                  (f4u*)(o4 + 4 * (j + u * NT)));
+      __builtin_nontemporal_store((f4u)dlogit4<ENT>(q[u], lk, c, e, mu, j + u * ST, yc),
+                                  (f4u*)(o4 + 4 * (j + u * ST)));
   }
-  for (; j < rv.n4; j += NT)
-    __builtin_nontemporal_store((f4u)dlogit4<ENT>(z4[j], lk, c, e, mu, j, yc), (f4u*)(o4 + 4 * j));
+  if constexpr (UN > 1 && ST == 64) {
+    if (j < rv.n4) {
+      floatx4 q[UN - 1];
+#pragma unroll
+      for (int u = 0; u < UN - 1; ++u) q[u] = z4[min(j + u * ST, rv.n4 - 1)];
+#pragma unroll
+      for (int u = 0; u < UN - 1; ++u)
+        if (j + u * ST < rv.n4)
+          __builtin_nontemporal_store((f4u)dlogit4<ENT>(q[u], lk, c, e, mu, j + u * ST, yc),
+                                      (f4u*)(o4 + 4 * (j + u * ST)));
+    }
+  } else {
+    for (; j < rv.n4; j += ST)
+      __builtin_nontemporal_store((f4u)dlogit4<ENT>(z4[j], lk, c, e, mu, j, yc), (f4u*)(o4 + 4 * j));
+  }
   if (rv.has_extra(vt)) {
     const int64_t i = rv.extra(vt);
     out[i] = dlogit1<ENT>(z[i], lk, c, e, mu, i == y);
@@ -188,10 +200,11 @@ __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, flo
 }
 
 // Zero a row of d_logits, 16-byte stores at its own boundaries.
+template <int ST = NT>
 __device__ void zero_row(float* __restrict__ out, int64_t V, int vt) {
   const RowView rv(out, V);
   const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t j = vt; j < rv.n4; j += NT) __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
+  for (int64_t j = vt; j < rv.n4; j += ST) __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
   if (rv.has_extra(vt)) out[rv.extra(vt)] = 0.f;
 }
 
@@ -228,9 +241,30 @@ __global__ void __launch_bounds__(NT) k_logits_stats(const float* __restrict__ l
   }
 }
 
-// ---- d_logits only (rft_ppo_clip_loss_bwd_logits); 2^lp workgroups per row, of
-// NT / 2^lp threads each
-template <bool ENT>
+// ---- d_logits only (rft_ppo_clip_loss_bwd_logits).  Row t by ST threads, this one
+// the vt-th.
+template <bool ENT, int UN, int ST>
+__device__ __forceinline__ void bwd_row(const float* __restrict__ logits, int64_t V, int64_t t,
+                                        int vt, const uint8_t* __restrict__ mask,
+                                        const int32_t* __restrict__ ids,
+                                        const float* __restrict__ lse,
+                                        const float* __restrict__ grad,
+                                        const float* __restrict__ egrad,
+                                        const float* __restrict__ ent, float* __restrict__ dl) {
+  float* out = dl + t * V;
+  if (!mask[t]) {
+    zero_row<ST>(out, V, vt);
+    return;
+  }
+  int y = ids[t];
+  const float L = lse[t];
+  const float e = ENT ? egrad[t] : 0.f, mu = ENT ? L - ent[t] : 0.f;
+  row_pass2<ENT, UN, ST>(logits + t * V, V, L, grad[t], e, mu,
+                         (y >= 0 && (int64_t)y < V) ? y : -1, out, vt);
+}
+
+// 2^lp workgroups per row, of NT / 2^lp threads each
+template <bool ENT, int UN>
 __global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ logits, int64_t V,
                                                     const uint8_t* __restrict__ mask,
                                                     const int32_t* __restrict__ ids,
@@ -241,15 +275,24 @@ __global__ void __launch_bounds__(NT) k_logits_bwd(const float* __restrict__ log
                                                     float* __restrict__ dl, int lp) {
   const int64_t t = blockIdx.x >> lp;
   const int vt = (int)(blockIdx.x & ((1u << lp) - 1)) * (NT >> lp) + threadIdx.x;
-  float* out = dl + t * V;
-  if (!mask[t]) {
-    zero_row(out, V, vt);
-    return;
-  }
-  int y = ids[t];
-  const float L = lse[t];
-  const float e = ENT ? egrad[t] : 0.f, mu = ENT ? L - ent[t] : 0.f;
-  row_pass2<ENT>(logits + t * V, V, L, grad[t], e, mu, (y >= 0 && (int64_t)y < V) ? y : -1, out, vt);
+  bwd_row<ENT, UN, NT>(logits, V, t, vt, mask, ids, lse, grad, egrad, ent, dl);
+}
+
+// Short rows: one wavefront per row, four rows per workgroup.  What bounds them is
+// the chain of a row's loads (mask, its scalars, its logits), so the rows in
+// flight count.  One wavefront against 512 threads per row: 96311 rows of 25 logits
+// 21.4 / 90 us, 49502 of 316 22.6 / 52, 20000 of 1001 29.2 / 30.7; from there on
+// the 512 threads are as fast or faster (8000 rows of 2047 25.1 / 22.3).
+constexpr int kShortRow = 1024, kShortT = 256;
+template <bool ENT, int UN>
+__global__ void __launch_bounds__(kShortT) k_logits_bwd_short(
+    const float* __restrict__ logits, int64_t T, int64_t V, const uint8_t* __restrict__ mask,
+    const int32_t* __restrict__ ids, const float* __restrict__ lse, const float* __restrict__ grad,
+    const float* __restrict__ egrad, const float* __restrict__ ent, float* __restrict__ dl) {
+  const int64_t t = (int64_t)blockIdx.x * (kShortT / 64) +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (t < T)
+    bwd_row<ENT, UN, 64>(logits, V, t, threadIdx.x & 63, mask, ids, lse, grad, egrad, ent, dl);
 }
 
 // ---- a handful of long rows: one workgroup per row leaves CUs idle, and a CU
@@ -353,7 +396,7 @@ __global__ void __launch_bounds__(NT) k_logits_fused(
   __syncthreads();
   float c = row_c, L = sh[NT / 64].m;
   int y = ids[t];
-  row_pass2<true>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out, threadIdx.x);
+  row_pass2<true, 8>(z, V, L, c, row_e, row_mu, (y >= 0 && (int64_t)y < V) ? y : -1, out, threadIdx.x);
 }
 
 // ---- fused, with the row kept on chip: the first REG*NTC float4 of the row
@@ -566,7 +609,23 @@ hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t
   int lp = 0;
   hipError_t e = row_parts(tok.T, V, &lp);
   if (e != hipSuccess) return e;
-  auto k = egrad ? lg::k_logits_bwd<true> : lg::k_logits_bwd<false>;
+  const bool en = egrad != nullptr;
+  if (V <= lg::kShortRow) {
+    auto k = V <= 256 ? (en ? lg::k_logits_bwd_short<true, 1> : lg::k_logits_bwd_short<false, 1>)
+                      : (en ? lg::k_logits_bwd_short<true, 4> : lg::k_logits_bwd_short<false, 4>);
+    for (int64_t t0 = 0; t0 < tok.T; t0 += kLaunchRows) {
+      const int64_t n = std::min(tok.T - t0, kLaunchRows);
+      k<<<(unsigned)((n + 3) / 4), lg::kShortT, 0, s>>>(logits + t0 * V, n, V, tok.mask + t0,
+                                                        tok.token_ids + t0, lse + t0, grad + t0,
+                                                        from(egrad, t0), from(ent, t0), dl + t0 * V);
+    }
+    return hipGetLastError();
+  }
+  // eight chunks in flight per thread where the rows leave CUs to spare; otherwise
+  // one, whose few registers let every wave slot fill (600 rows of 151936: 139 us
+  // against 145 with eight, 2048 of 32000 75 with either)
+  auto k = lp > 0 ? (en ? lg::k_logits_bwd<true, 8> : lg::k_logits_bwd<false, 8>)
+                  : (en ? lg::k_logits_bwd<true, 1> : lg::k_logits_bwd<false, 1>);
   for (int64_t t0 = 0; t0 < tok.T; t0 += kLaunchRows) {
     const int64_t n = std::min(tok.T - t0, kLaunchRows);
     k<<<(unsigned)(n << lp), lg::NT >> lp, 0, s>>>(logits + t0 * V, V, tok.mask + t0,
