@@ -205,11 +205,12 @@ __device__ __forceinline__ float adv_value(int mode, bool degenerate, double v, 
   return (float)a;
 }
 
-// Few rollouts (at most kAdvFew): one launch instead of eight (17 us at 128
-// rollouts).  Every thread takes one rollout and walks all ids and rewards (in
-// LDS) twice, adding its own group's in index order; the walk is kAdvFew long,
-// past which the bucketed path is the faster one (1024: 12 us against 18).
-constexpr int kAdvFew = 1024;
+// Few rollouts (at most kAdvFew): one launch instead of eight.  Every thread takes
+// one rollout and walks all ids and rewards (in LDS) twice, adding its own group's
+// in index order; the walk is kAdvFew long, past which the bucketed path is the
+// faster one.  Whole call, walk against buckets: 128 rollouts 10 / 29 us, 256 14 / 29,
+// 512 26 / 29, 640 32 / 29, 1024 48 / 29.
+constexpr int kAdvFew = 512;
 __global__ void __launch_bounds__(256) k_adv_few(const float* __restrict__ r,
                                                  const int32_t* __restrict__ gid, int n,
                                                  int64_t n_groups, int mode, float eps,

@@ -66,10 +66,10 @@ def test_counts_and_loss_sums(T, n_seq, shift):
 
 
 @pytest.mark.parametrize("mode", [R.RFT_ADV_GRPO, R.RFT_ADV_MEAN_CENTER, R.RFT_ADV_LEAVE_ONE_OUT])
-@pytest.mark.parametrize("n,n_groups", [(1, 1), (3, 2), (256, 300), (257, 31), (1023, 1), (1024, 64),
-                                        (1025, 64)])
+@pytest.mark.parametrize("n,n_groups", [(1, 1), (3, 2), (256, 300), (257, 31), (511, 3), (512, 64),
+                                        (513, 64), (1023, 1), (1024, 64), (1025, 64)])
 def test_advantages_of_few_rollouts(n, n_groups, mode):
-    """One launch up to 1024 rollouts, the bucketed path past them: fp64 sums
+    """One launch up to 512 rollouts, the bucketed path past them: fp64 sums
     rounded once to fp32 (2^-24 of the result; 1e-12 for the sums' order)."""
     r = np.random.default_rng(7 * n + mode)
     rew = r.random(n).astype(np.float32)
@@ -90,3 +90,29 @@ def test_advantages_of_few_rollouts(n, n_groups, mode):
         else:
             want[k] = v - (v.sum() - v) / (v.size - 1)
     assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want) + 1e-12).all()
+
+
+def test_advantages_take_the_faster_path():
+    """1000 rollouts by buckets, like 1500 (by one launch they took 1.6 times as long)."""
+
+    def us(n):
+        rew = torch.rand(n, device=DEV)
+        gid = torch.randint(0, n // 8, (n,), device=DEV, dtype=torch.int32)
+        ws = torch.empty(R.lib().rft_group_advantages_ids_workspace_bytes(n, n // 8),
+                         dtype=torch.uint8, device=DEV)
+        out = torch.empty_like(rew)
+        ts = []
+        for i in range(25):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                R.rft_group_advantages_ids(rew, gid, n // 8, out=out, ws=ws)
+            b.record()
+            b.synchronize()
+            ts.append(a.elapsed_time(b) * 125)
+        return sorted(ts)[8]
+
+    us(1000)
+    a, b = us(1000), us(1500)
+    print(f"[advantages] 1000: {a:.1f} us, 1500: {b:.1f} us", flush=True)
+    assert a <= 1.35 * b
