@@ -13,9 +13,10 @@
 // so that one's loads run under another's stores.
 // A row is cut at the 16-byte boundaries of its logits (RowView): up to three
 // elements before the first, whole chunks of four, up to three after the last;
-// V and the base need no alignment.  Every kernel here gives each thread the
-// same chunks of the row in the same order, so the statistics-only,
-// d_logits-only and fused kernels agree bit for bit.
+// V and the base need no alignment.  Every kernel that forms statistics gives
+// each thread the same chunks of the row in the same order, and an element of
+// d_logits depends on the row's statistics and its own logit only, so the
+// statistics-only, d_logits-only and fused kernels agree bit for bit.
 #include <algorithm>
 
 #include "rft_internal.h"
