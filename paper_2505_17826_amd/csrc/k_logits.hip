@@ -200,12 +200,16 @@ __device__ void row_pass2(const float* __restrict__ z, int64_t V, float lse, flo
   }
 }
 
-// Zero a row of d_logits, 16-byte stores at its own boundaries.
-template <int ST = NT>
+// Zero a row of d_logits, 16-byte stores at its own boundaries (NTS: non-temporal).
+template <int ST = NT, bool NTS = true>
 __device__ void zero_row(float* __restrict__ out, int64_t V, int vt) {
   const RowView rv(out, V);
   const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
-  for (int64_t j = vt; j < rv.n4; j += ST) __builtin_nontemporal_store(zz, (floatx4*)rv.z4 + j);
+  for (int64_t j = vt; j < rv.n4; j += ST) {
+    floatx4* const o = (floatx4*)rv.z4 + j;
+    if (NTS) __builtin_nontemporal_store(zz, o);
+    else *o = zz;
+  }
   if (rv.has_extra(vt)) out[rv.extra(vt)] = 0.f;
 }
 
@@ -449,12 +453,18 @@ __global__ void __launch_bounds__(NTC, WPS) k_logits_fused_cached(
   const uint32_t vo = (uint32_t)tid * 16u;
   constexpr uint32_t SU = (uint32_t)NTC * 16u;  // bytes between a thread's chunks
   if (k < 0) {
+    // Where two or three workgroups share a CU, masked rows are cleared by ordinary
+    // stores: 17622 rows of 27176 logits, 90% masked, 530 -> 461 us (one workgroup
+    // per CU took 490), 10% masked 742 -> 709; 4000 of 50001 236 -> 201 and 324 ->
+    // 312.  With four (60000 rows of 4000: 410 -> 422) and with one (8192 of 151936,
+    // half masked: 1409 -> 1448) the non-temporal ones are faster.
+    constexpr bool NTS = LCH == 0 || WPS == 2;
     if (AL) {
       const floatx4 zz = {0.f, 0.f, 0.f, 0.f};
       for (int64_t j = tid, o = vo; j < n4; j += NTC, o += SU)
-        __builtin_amdgcn_raw_buffer_store_b128((v4i)zz, rout, (uint32_t)o, 0, 2);
+        __builtin_amdgcn_raw_buffer_store_b128((v4i)zz, rout, (uint32_t)o, 0, NTS ? 2 : 0);
     } else {
-      zero_row(out, V, threadIdx.x);
+      zero_row<NT, NTS>(out, V, threadIdx.x);
     }
     if (tid == 0) {
       logp[t] = 0.f;
