@@ -632,11 +632,14 @@ hipError_t launch_logits_bwd(const float* logits, const rft_tokens& tok, int64_t
     }
     return hipGetLastError();
   }
-  // eight chunks in flight per thread where the rows leave CUs to spare; otherwise
-  // one, whose few registers let every wave slot fill (600 rows of 151936: 139 us
-  // against 145 with eight, 2048 of 32000 75 with either)
-  auto k = lp > 0 ? (en ? lg::k_logits_bwd<true, 8> : lg::k_logits_bwd<false, 8>)
-                  : (en ? lg::k_logits_bwd<true, 1> : lg::k_logits_bwd<false, 1>);
+  // eight chunks in flight per thread where the rows leave CUs to spare, and for
+  // rows of two to four such batches; otherwise one, whose few registers let every
+  // wave slot fill.  One against eight: 600 rows of 151936 139 / 145 us, 8192 of them
+  // 1945 / 2015, 60000 of 4000 303 / 327; 4096 of 32000 205 / 202, 4000 of 60000 378 /
+  // 372.
+  const bool eight = lp > 0 || (V > 16384 && V <= 65536);
+  auto k = eight ? (en ? lg::k_logits_bwd<true, 8> : lg::k_logits_bwd<false, 8>)
+                 : (en ? lg::k_logits_bwd<true, 1> : lg::k_logits_bwd<false, 1>);
   for (int64_t t0 = 0; t0 < tok.T; t0 += kLaunchRows) {
     const int64_t n = std::min(tok.T - t0, kLaunchRows);
     k<<<(unsigned)(n << lp), lg::NT >> lp, 0, s>>>(logits + t0 * V, V, tok.mask + t0,
