@@ -40,13 +40,13 @@ TRAFFIC = {
     # forward GEMM alone (k_gemm384<EPI_STATS> on the tile-blocked copies, one launch over
     # all valid rows)
     "7b": {"sources": {'k_gemm_mfma.hip': '0cc59ef48596356f', 'rft_internal.h': 'a778fbc47a9f52d0'},
-           "bytes": 171001716.1 * 1024 * 2.0 + 1174431.1 * 1024 * 1.0},
+           "bytes": 172748926.9 * 1024 * 2.0 + 1174430.6 * 1024 * 1.0},
     # every kernel of one rft_ppo_clip_step call and its advantages (24 dispatches, two
     # row chunks)
-    "step_7b": {"sources": {'k_gemm_mfma.hip': '0cc59ef48596356f', 'k_step.hip': 'a920d8a6385f4246', 'k_layout.hip': '59fafc69e9c8b096', 'k_adv_loss.hip': '3e2b860017848fdf', 'k_tokens.hip': '2e004762720e0e21', 'tokens_device.h': '73eabd5a3070690d', 'rft_internal.h': 'a778fbc47a9f52d0', 'rft_abi.hip': '0a71af3bbc7c6fe8'},
-                "bytes": 625386268.1 * 1024 * 2.0 + 164161177.3 * 1024 * 1.0},
-    "lossonly": {"sources": {'k_logits.hip': '4e0ce80d9e03b5ba', 'rft_internal.h': 'a778fbc47a9f52d0'},
-                 "bytes": 8758802.7 * 1024 * 2.0 + 19480270.7 * 1024 * 1.0},
+    "step_7b": {"sources": {'k_gemm_mfma.hip': '0cc59ef48596356f', 'k_step.hip': 'a920d8a6385f4246', 'k_layout.hip': '59fafc69e9c8b096', 'k_adv_loss.hip': '20f27cec6e4001a4', 'k_tokens.hip': '2e004762720e0e21', 'tokens_device.h': 'd5c28753c1c6f594', 'rft_internal.h': 'a778fbc47a9f52d0', 'rft_abi.hip': '0a71af3bbc7c6fe8'},
+                "bytes": 616371101.2 * 1024 * 2.0 + 164158424.2 * 1024 * 1.0},
+    "lossonly": {"sources": {'k_logits.hip': '4ea4f0a25bbfcd3f', 'rft_internal.h': 'a778fbc47a9f52d0'},
+                 "bytes": 8758803.0 * 1024 * 2.0 + 19480261.2 * 1024 * 1.0},
 }
 
 
